@@ -85,29 +85,56 @@ struct Footprint {
     float s, t;    // position inside the footprint, in [0,1)
 };
 
+// No branches: a NaN or infinite u or v leaves fx or fy NaN or infinite, so
+// the range test alone decides `active`, and the other members of an
+// inactive lane are unused values.
 __device__ __forceinline__ Footprint footprint(float u, float v, float4 d, float W, float H)
 {
     Footprint f;
-    f.active = false;
-    f.magnify = false;
-    f.x0 = f.y0 = 0;
-    f.s = f.t = 0.f;
-    if (!__builtin_isfinite(u) || !__builtin_isfinite(v)) return f;
     const float fx = __builtin_fmaf(u, W, -0.5f);
     const float fy = __builtin_fmaf(v, H, -0.5f);
-    if (!(__builtin_fabsf(fx) < kRange) || !(__builtin_fabsf(fy) < kRange)) return f;
+    f.active = __builtin_fabsf(fx) < kRange && __builtin_fabsf(fy) < kRange;
     const float flx = __builtin_floorf(fx), fly = __builtin_floorf(fy);
     f.x0 = (int)flx;
     f.y0 = (int)fly;
     f.s = fx - flx;
     f.t = fy - fly;
-    f.active = true;
     const float a = d.x * W, b = d.y * H, c = d.z * W, e = d.w * H;
     const float rx2 = __builtin_fmaf(a, a, b * b);
     const float ry2 = __builtin_fmaf(c, c, e * e);
-    f.magnify = (rx2 <= 1.0f) && (ry2 <= 1.0f);
+    f.magnify = rx2 <= 1.0f && ry2 <= 1.0f;
     return f;
 }
+
+// The footprint with the wave's decisions as lane masks: act (active lanes)
+// and A (active and magnifying).  Each mask is an AND of compare results in
+// scalar registers.
+struct WaveFootprint {
+    uint64_t act, A;
+    int x0, y0;
+    float s, t;
+};
+
+__device__ __forceinline__ WaveFootprint wave_footprint(float u, float v, float4 d, float W, float H)
+{
+    WaveFootprint f;
+    const float fx = __builtin_fmaf(u, W, -0.5f);
+    const float fy = __builtin_fmaf(v, H, -0.5f);
+    f.act = ballot(__builtin_fabsf(fx) < kRange) & ballot(__builtin_fabsf(fy) < kRange);
+    const float flx = __builtin_floorf(fx), fly = __builtin_floorf(fy);
+    f.x0 = (int)flx;
+    f.y0 = (int)fly;
+    f.s = fx - flx;
+    f.t = fy - fly;
+    const float a = d.x * W, b = d.y * H, c = d.z * W, e = d.w * H;
+    const float rx2 = __builtin_fmaf(a, a, b * b);
+    const float ry2 = __builtin_fmaf(c, c, e * e);
+    f.A = f.act & ballot(rx2 <= 1.0f) & ballot(ry2 <= 1.0f);
+    return f;
+}
+
+// This lane's bit of a wave-uniform mask, as a predicate.
+__device__ __forceinline__ bool lane_in(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
 
 // Bilinear filtering of texels v0 = (x0,y0), v1 = (x0+1,y0), v2 = (x0,y0+1),
 // v3 = (x0+1,y0+1) as two lerps in x and one in y, lerp(a, b, s) =
@@ -284,6 +311,69 @@ __device__ __forceinline__ void footprint_mask_f(const uint64_t C[4], uint64_t B
             B[w] = Hm[w] | (Hm[w] << 16) | (lo >> 48) | (Hm[w] << 32) | (lo >> 32) | (Hm[w] << 48) | (lo >> 16);
         }
     }
+}
+
+// Wave-wide inclusive sum (all 64 lanes active): DPP shifts inside the rows
+// of 16 lanes, then the row totals broadcast to the rows behind.
+__device__ __forceinline__ int wave_scan(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15 to rows 1, 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31 to rows 2, 3
+    return v;
+}
+
+// The distinct texels of a 16x16 window, four positions per lane: lane l
+// holds positions 4l..4l+3 (window row l/4, columns 4 (l%4)..+3).
+struct WindowSet {
+    uint32_t set;     // byte q: 1 if position 4l+q is needed by some lane
+    uint32_t ranks;   // byte q: number of needed positions before 4l+q (row-major)
+    int n;            // needed positions in all
+};
+
+// LDS of window_set: 64 words of position bytes behind 16 words that stay
+// zero (kWindowPad; the caller clears them once).
+constexpr int kWindowPad = 16;
+constexpr int kWindowWords = kWindowPad + kWave;
+
+// Each lane of A marks its footprint's corner byte; the FxF spread of the
+// marks is then a few byte shifts of the words of rows r, r-1, .. r-F+1 (a
+// corner sits at column <= 16 - F, so the bytes shifted in from the previous
+// word of the same row never cross a row), and the ranks are one wave-wide
+// sum.  One LDS round trip and no mask in scalar registers: the earlier form
+// (four byte reads, four ballots, 256-bit scalar shifts, a rank per ballot)
+// took four serial LDS round trips and about 130 scalar instructions.
+template <int F>
+__device__ __forceinline__ WindowSet window_set(uint32_t* words, bool inA, int corner)
+{
+    const int lane = lane_id();
+    uint32_t* const w = words + kWindowPad + lane;
+    *w = 0u;
+    wave_lds_sync();
+    if (inA) reinterpret_cast<uint8_t*>(words + kWindowPad)[corner] = 1;
+    wave_lds_sync();
+    uint32_t cur = 0u, prev = 0u;
+#pragma unroll
+    for (int r = 0; r < F; ++r) {
+        cur |= w[-4 * r];
+        prev |= w[-4 * r - 1];
+    }
+    WindowSet S;
+    S.set = cur;
+#pragma unroll
+    for (int c = 1; c < F; ++c) S.set |= __builtin_amdgcn_alignbyte(cur, prev, 4 - c);
+    const int cnt = (int)__builtin_amdgcn_sad_u8(S.set, 0u, 0u);
+    const int incl = wave_scan(cnt);
+    S.n = __builtin_amdgcn_readlane(incl, 63);
+    // exclusive byte sums inside the word, plus the lane's base in each byte
+    // (a rank is below 256, so no byte carries)
+    uint32_t t = S.set + (S.set << 8);
+    t += t << 16;
+    S.ranks = (t << 8) + __builtin_amdgcn_perm(0u, (uint32_t)(incl - cnt), 0u);
+    return S;
 }
 
 // A wave's walk over tiles t0, t0 + step, ... of a row-major tile grid,

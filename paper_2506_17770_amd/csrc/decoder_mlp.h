@@ -287,36 +287,41 @@ struct InferGrid {
     int tex_w;
 };
 
-// Per-lane constants of the inference fetch (level g/2, channels 4 (g%2)..+3).
+// The latent reads of a decode go 32 texels at a time: lane l reads the eight
+// channels of level l/32 for texel l%32, one 16-byte load per corner.  (With
+// 16 texels a lane holds four channels and the same bytes take twice as many
+// loads and address computations; a wave's gather occupies the vector L1 for
+// about 20 cycles whether its lanes ask for 8 or 16 bytes.)  After the
+// interpolation the two 16-texel operands of layer 1 are one exchange of
+// 16-lane rows away (infer_combine).
+
+// Per-lane constants of the inference fetch (one latent level).
 template <int P>
 struct InferLane {
-    uint32_t off;      // byte offset of the level plus 8 (g % 2)
+    uint32_t off;      // byte offset of the level
     uint32_t pitch;    // L + 1 cells
     uint32_t c;        // 1 - 2^s
     uint32_t sh;       // s + 1
     uint32_t logl;     // log2 L
     float scale;       // 2^-(s+1)
 
-    __device__ __forceinline__ InferLane(const InferGrid& G, int g)
+    __device__ __forceinline__ InferLane(const InferGrid& G, bool l1)
     {
-        const bool l1 = g >= 2;
         const int s = l1 ? G.shift1 : G.shift0;
         logl = (uint32_t)(l1 ? G.log_l1 : G.log_l0);
         pitch = (1u << logl) + 1u;
-        off = (l1 ? G.lvl1 : 0u) + 8u * (uint32_t)(g & 1);
+        off = l1 ? G.lvl1 : 0u;
         c = 1u - (1u << s);
         sh = (uint32_t)s + 1u;
         scale = __builtin_bit_cast(float, (uint32_t)(127 - s - 1) << 23);
     }
 };
 
-// The four corner vectors and the bilinear weights of one sample; fp16:
-// weights packed as (w0, w1), (w2, w3) -- each a multiple of 2^-2(s+1) below
-// 1, so exact in fp16 for s <= 4 (rounded to fp16 beyond); bf16: float.
+// The four corner vectors of one sample and the integers its position comes
+// from.
 struct InferFetch {
-    u16x4 v[4];
-    uint32_t w01, w23;
-    float w[4];
+    u32x4 v[4];
+    uint32_t gx, gy;
 };
 
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
@@ -324,72 +329,78 @@ typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 template <int P>
 __device__ __forceinline__ void infer_fetch(const InferGrid& G, const InferLane<P>& K, int x, int y, InferFetch& F)
 {
-    const uint32_t gx = 2u * (uint32_t)x + K.c, gy = 2u * (uint32_t)y + K.c;
-    const uint32_t cx = __builtin_amdgcn_ubfe(gx, K.sh, K.logl);
-    const uint32_t cy = __builtin_amdgcn_ubfe(gy, K.sh, K.logl);
-    const float fx = (float)__builtin_amdgcn_ubfe(gx, 0u, K.sh) * K.scale;
-    const float fy = (float)__builtin_amdgcn_ubfe(gy, 0u, K.sh) * K.scale;
+    F.gx = 2u * (uint32_t)x + K.c;
+    F.gy = 2u * (uint32_t)y + K.c;
+    const uint32_t cx = __builtin_amdgcn_ubfe(F.gx, K.sh, K.logl);
+    const uint32_t cy = __builtin_amdgcn_ubfe(F.gy, K.sh, K.logl);
     const uint32_t o0 = (__umul24(cy, K.pitch) + cx) * 16u + K.off;
     const uint32_t o1 = o0 + K.pitch * 16u;
     const char* __restrict__ b = reinterpret_cast<const char*>(G.base);
-    F.v[0] = *reinterpret_cast<const u16x4*>(b + o0);
-    F.v[1] = *reinterpret_cast<const u16x4*>(b + o0 + 16u);
-    F.v[2] = *reinterpret_cast<const u16x4*>(b + o1);
-    F.v[3] = *reinterpret_cast<const u16x4*>(b + o1 + 16u);
-    if (P == CTF_FP16) {
+    F.v[0] = *reinterpret_cast<const u32x4*>(b + o0);
+    F.v[1] = *reinterpret_cast<const u32x4*>(b + o0 + 16u);
+    F.v[2] = *reinterpret_cast<const u32x4*>(b + o1);
+    F.v[3] = *reinterpret_cast<const u32x4*>(b + o1 + 16u);
+}
+
+// The interpolated features of the 32 samples as layer-1 B operands: xa for
+// texels 0..15, xb for texels 16..31 (lane l: features 4 (l/16)..+3 of texel
+// l%16).  fp16: packed fp16 weights, products and sums (v_pk_mul / v_pk_fma,
+// each rounding to fp16; the weights are multiples of 2^-2(s+1) below 1, so
+// exact for s <= 4); bf16: float32 sums rounded once.
+template <int P>
+__device__ __forceinline__ void infer_combine(const InferFetch& F, const InferLane<P>& K, u16x4& xa, u16x4& xb)
+{
+    const float fx = (float)__builtin_amdgcn_ubfe(F.gx, 0u, K.sh) * K.scale;
+    const float fy = (float)__builtin_amdgcn_ubfe(F.gy, 0u, K.sh) * K.scale;
+    u32x4 r;   // channels 0..7 of this lane's level and texel
+    if constexpr (P == CTF_FP16) {
         const h2 f = __builtin_bit_cast(h2, cvt2<CTF_FP16>(fx, fy));
         const h2 one = {(_Float16)1.0f, (_Float16)1.0f};
         const h2 i = one - f;                                       // (1 - fx, 1 - fy)
-        const h2 r = __builtin_shufflevector(i, f, 0, 2);           // (1 - fx, fx)
-        F.w01 = __builtin_bit_cast(uint32_t, r * __builtin_shufflevector(i, i, 1, 1));
-        F.w23 = __builtin_bit_cast(uint32_t, r * __builtin_shufflevector(f, f, 1, 1));
-    } else {
-        const float ifx = 1.0f - fx, ify = 1.0f - fy;
-        F.w[0] = ifx * ify;
-        F.w[1] = fx * ify;
-        F.w[2] = ifx * fy;
-        F.w[3] = fx * fy;
-    }
-}
-
-// The interpolated features of the sample as the layer-1 B operand.  fp16:
-// packed fp16 products and sums (v_pk_mul / v_pk_fma, each rounding to
-// fp16); bf16: float32 sums rounded once.
-template <int P>
-__device__ __forceinline__ u16x4 infer_combine(const InferFetch& F)
-{
-    if (P == CTF_FP16) {
-        const h2 w01 = __builtin_bit_cast(h2, F.w01), w23 = __builtin_bit_cast(h2, F.w23);
+        const h2 t = __builtin_shufflevector(i, f, 0, 2);           // (1 - fx, fx)
+        const h2 w01 = t * __builtin_shufflevector(i, i, 1, 1), w23 = t * __builtin_shufflevector(f, f, 1, 1);
         const h2 ws[4] = {__builtin_shufflevector(w01, w01, 0, 0), __builtin_shufflevector(w01, w01, 1, 1),
                           __builtin_shufflevector(w23, w23, 0, 0), __builtin_shufflevector(w23, w23, 1, 1)};
-        // (a subscript applied directly to a __builtin_bit_cast result is
-        // miscompiled by this clang -- it reads element 0 -- so every
-        // reinterpreted vector is named before it is indexed)
-        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-        u32x2 d[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) d[q] = __builtin_bit_cast(u32x2, F.v[q]);
-        u32x2 r;
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            const uint32_t d0 = d[0][half];
+        for (int p = 0; p < 4; ++p) {
+            // (a subscript applied directly to a __builtin_bit_cast result is
+            // miscompiled by this clang -- it reads element 0 -- so every
+            // reinterpreted word is named before it is used)
+            const uint32_t d0 = F.v[0][p];
             h2 acc = __builtin_bit_cast(h2, d0) * ws[0];
 #pragma unroll
             for (int q = 1; q < 4; ++q) {
-                const uint32_t dq = d[q][half];
+                const uint32_t dq = F.v[q][p];
                 acc = __builtin_elementwise_fma(__builtin_bit_cast(h2, dq), ws[q], acc);
             }
-            r[half] = __builtin_bit_cast(uint32_t, acc);
+            r[p] = __builtin_bit_cast(uint32_t, acc);
         }
-        return __builtin_bit_cast(u16x4, r);
     } else {
-        f4 x = {0.f, 0.f, 0.f, 0.f};
+        const float ifx = 1.0f - fx, ify = 1.0f - fy;
+        const float ws[4] = {ifx * ify, fx * ify, ifx * fy, fx * fy};
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (int p = 0; p < 4; ++p) {
+            float lo = 0.f, hi = 0.f;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) x[i] = __builtin_fmaf(F.w[q], Mfma<P>::load(F.v[q][i]), x[i]);
-        return pack4<P>(x);
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t dq = F.v[q][p];
+                lo = __builtin_fmaf(ws[q], __uint_as_float(dq << 16), lo);
+                hi = __builtin_fmaf(ws[q], __uint_as_float(dq & 0xffff0000u), hi);
+            }
+            r[p] = cvt2<P>(lo, hi);
+        }
     }
+    // Row s of 16 lanes holds level s/2 of texels 16 (s%2)..+15: words 0, 1
+    // are its channels 0..3, words 2, 3 its channels 4..7.  Swapping the odd
+    // rows of the first with the even rows of the second leaves, row by row,
+    // (level 0, ch 0..3), (level 0, ch 4..7), (level 1, ...) of texels 0..15
+    // in the first and of texels 16..31 in the second.
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 p0 = __builtin_amdgcn_permlane16_swap(r[0], r[2], false, false);
+    const u32x2 p1 = __builtin_amdgcn_permlane16_swap(r[1], r[3], false, false);
+    const u32x2 a = {p0[0], p1[0]}, b = {p0[1], p1[1]};
+    xa = __builtin_bit_cast(u16x4, a);
+    xb = __builtin_bit_cast(u16x4, b);
 }
 
 // Forward pass of 16 texels whose features this lane holds (xb = features

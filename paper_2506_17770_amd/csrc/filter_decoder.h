@@ -22,6 +22,8 @@
 
 #include <stddef.h>
 
+#include <type_traits>
+
 #include "ctf_device.h"
 #include "ctf_internal.h"
 #include "decoder_mlp.h"
@@ -32,6 +34,8 @@ namespace ctf {
 namespace dec {
 
 constexpr int kDecWaves = 4;
+
+constexpr bool collaborative(int m) { return m == CTF_LIST || m == CTF_BOX || m == CTF_MASK; }
 
 // vals, rows and keys are contiguous: the bicubic List sort uses the three
 // as one 1024-key buffer before any row or value exists.
@@ -55,25 +59,27 @@ __device__ __forceinline__ uint64_t* dec_keys(DecLds& L)
 
 // Exact set of the wave's texels as sorted unique keys (any box size): a
 // bitonic sort of the F^2 |A| footprint keys, then compaction of the first
-// key of every run.  Returns n = |U|; dec_keys<F>(L)[0..n) hold U in (y, x)
-// order.
+// key of every run (rolled loops: few waves take this path, and unrolled it
+// costs the common path registers).  Returns n = |U|; keys[0..n) hold U in (y, x) order (keys:
+// F^2 x 64 entries).
 template <int F>
-__device__ int dec_list_sorted(DecLds& L, bool inA, int ox, int oy, int xmin, int ymin)
+__device__ __forceinline__ int dec_list_sorted(uint64_t* keys, bool inA, int ox, int oy, int xmin, int ymin)
 {
     constexpr int N = kWave * F * F;
-    uint64_t* keys = dec_keys<F>(L);
     const int lane = lane_id();
-#pragma unroll
+#pragma unroll 1
     for (int q = 0; q < F * F; ++q) {
         uint64_t key = ~0ull;
         if (inA)
             key = ((uint64_t)(uint32_t)(oy + q / F - ymin) << 32) | (uint32_t)(ox + q % F - xmin);
         keys[F * F * lane + q] = key;
     }
+#pragma unroll 1
     for (int size = 2; size <= N; size <<= 1)
+#pragma unroll 1
         for (int stride = size >> 1; stride > 0; stride >>= 1) {
             wave_lds_sync();
-#pragma unroll
+#pragma unroll 1
             for (int h = 0; h < N / (2 * kWave); ++h) {
                 const int p = lane + kWave * h;
                 const int i = (p / stride) * stride * 2 + (p % stride);
@@ -89,6 +95,7 @@ __device__ int dec_list_sorted(DecLds& L, bool inA, int ox, int oy, int xmin, in
     // compaction in rounds of 64 keys: a write index never passes the read
     // index, and round r writes below every key of the later rounds
     int base = 0;
+#pragma unroll 1
     for (int c = 0; c < F * F; ++c) {
         wave_lds_sync();
         const int i = kWave * c + lane;
@@ -127,38 +134,45 @@ __device__ __forceinline__ void fetch_row(const int2* rows, int row, const Infer
 
 template <int P>
 __device__ __forceinline__ void finish_row(float4* vals, int R, int row, const FwdWeights<P>& W,
-                                           const Biases& Bz, const InferFetch& F, int g)
+                                           const Biases& Bz, u16x4 x, int g)
 {
-    const f4 y = mlp_forward_b<P>(W, Bz, infer_combine<P>(F), nullptr, nullptr);
+    const f4 y = mlp_forward_b<P>(W, Bz, x, nullptr, nullptr);
     if (g == 0 && row < R) vals[row] = make_float4(y[0], y[1], y[2], y[3]);
 }
 
-// rows[0..R) -> vals[0..R) in 16-row tiles, two fetch buffers in ping-pong.
-// Every prefetch is issued unconditionally, so each path reaches the next
-// tile's MLP with the same loads outstanding and the wait before it covers
-// only the current tile's gathers.
+// rows[0..R) -> vals[0..R): latents 32 rows at a time, the MLP on 16-row
+// tiles (the last 32 rows may hold one).  The next 32 rows' gathers are
+// issued, unconditionally, once the current features are interpolated, so
+// they are in flight during two MLP passes.
 template <int P>
-__device__ __forceinline__ void decode_rows(DecLds& L, int R, const InferGrid& G, const FwdWeights<P>& W,
-                                            const Biases& Bz, int j, int g)
+__device__ __forceinline__ void decode_rows(const int2* rows, float4* vals, int R, const InferGrid& G,
+                                            const FwdWeights<P>& W, const Biases& Bz)
 {
-    const int T = (R + 15) >> 4;
-    if (T == 0) return;
-    const InferLane<P> K(G, g);
-    InferFetch fa, fb;
-    fetch_row<P>(L.rows, j, G, K, fa);
-    for (int t = 0; t < T; t += 2) {
-        fetch_row<P>(L.rows, 16 * (t + 1) + j, G, K, fb);
-        finish_row<P>(L.vals, R, 16 * t + j, W, Bz, fa, g);
-        if (t + 1 >= T) break;
-        fetch_row<P>(L.rows, 16 * (t + 2) + j, G, K, fa);
-        finish_row<P>(L.vals, R, 16 * (t + 1) + j, W, Bz, fb, g);
+    if (R == 0) return;
+    const int j = lane_id() & 15, g = lane_id() >> 4;
+    const InferLane<P> K(G, g >= 2);
+    const int jf = j + 16 * (g & 1);
+    InferFetch F;
+    u16x4 xa, xb;
+    fetch_row<P>(rows, jf, G, K, F);
+    int r0 = 0;
+    for (; r0 + 16 < R; r0 += 32) {
+        infer_combine<P>(F, K, xa, xb);
+        fetch_row<P>(rows, r0 + 32 + jf, G, K, F);
+        finish_row<P>(vals, R, r0 + j, W, Bz, xa, g);
+        finish_row<P>(vals, R, r0 + 16 + j, W, Bz, xb, g);
     }
-    // The last prefetch (issued during the last MLP) is never used: wait for
-    // it here, while it is nearly done, rather than where its registers are
-    // next written, which may be after the next tile's inputs were requested
-    // (memory counters drain in order, so that wait would cover them too).
-    asm volatile("" ::"v"(fa.v[0]), "v"(fa.v[1]), "v"(fa.v[2]), "v"(fa.v[3]), "v"(fb.v[0]), "v"(fb.v[1]),
-                 "v"(fb.v[2]), "v"(fb.v[3]));
+    // With 16 rows or fewer left the last fetch is theirs.  Otherwise it is
+    // never used: wait for it here, while it is nearly done, rather than
+    // where its registers are next written, which may be after the next
+    // tile's inputs were requested (memory counters drain in order, so that
+    // wait would cover them too).
+    if (r0 < R) {
+        infer_combine<P>(F, K, xa, xb);
+        finish_row<P>(vals, R, r0 + j, W, Bz, xa, g);
+    } else {
+        asm volatile("" ::"v"(F.v[0]), "v"(F.v[1]), "v"(F.v[2]), "v"(F.v[3]));
+    }
 }
 
 __device__ __forceinline__ void write_tile_stats(const FilterArgs& a, int64_t tile, uint64_t act, uint64_t A,
@@ -197,7 +211,6 @@ __device__ __forceinline__ void dec_tile(const FilterArgs& a, const InferGrid& G
 {
     constexpr int F = Taps<FILTER>::F, O = Taps<FILTER>::O;
     const int lane = lane_id();
-    const int j = lane & 15, g = lane >> 4;
     const int px = tx * kTile + (lane & 7), py = ty * kTile + (lane >> 3);
     const bool in_screen = px < a.sw && py < a.sh;
     const int64_t pix = (int64_t)py * a.sw + px;
@@ -254,7 +267,7 @@ __device__ __forceinline__ void dec_tile(const FilterArgs& a, const InferGrid& G
         success = fits16 && count_ok;
     } else if constexpr (METHOD == CTF_LIST) {
         if (nA > 0 && !fits16) {
-            n = dec_list_sorted<F>(L, inA, ox, oy, xmin, ymin);
+            n = dec_list_sorted<F>(dec_keys<F>(L), inA, ox, oy, xmin, ymin);
             sorted = true;
         } else {
             n = nmask;
@@ -264,7 +277,7 @@ __device__ __forceinline__ void dec_tile(const FilterArgs& a, const InferGrid& G
         success = nA > 0 && count_ok;
     }
     if constexpr (STATS && METHOD != CTF_LIST) {
-        if (nA > 0 && !fits16) unique = dec_list_sorted<F>(L, inA, ox, oy, xmin, ymin);
+        if (nA > 0 && !fits16) unique = dec_list_sorted<F>(dec_keys<F>(L), inA, ox, oy, xmin, ymin);
     }
     if (nA == 0) unique = 0;
 
@@ -301,7 +314,7 @@ __device__ __forceinline__ void dec_tile(const FilterArgs& a, const InferGrid& G
                 for (int i = 0; i < 4; ++i) L.rows[4 * rank_act + i] = make_int2(ox + i, oy + jr);
             }
             wave_lds_sync();
-            decode_rows<P>(L, R, G, W, Bz, j, g);
+            decode_rows<P>(L.rows, L.vals, R, G, W, Bz);
             if (jr == 0) after_decode();
             wave_lds_sync();
             if (exact) {
@@ -415,7 +428,7 @@ __device__ __forceinline__ void dec_tile(const FilterArgs& a, const InferGrid& G
 
     // ---- decode the rows, 16 per MFMA tile; the latent gathers of the
     // next tile are in flight during the MLP of the current one
-    decode_rows<P>(L, R, G, W, Bz, j, g);
+    decode_rows<P>(L.rows, L.vals, R, G, W, Bz);
     after_decode();
     wave_lds_sync();
 
@@ -659,98 +672,106 @@ __global__ __launch_bounds__(64 * kDecWaves, (dec_waves_per_simd<METHOD, FILTER>
 }
 
 // ---------------------------------------------------------------------------
-// Batched decode (bilinear filter, no C / C+ fallback).  A wave plans each
-// tile into a staging row list, then appends the rows to the decode batch;
-// the batch of up to two tiles (at most 256 rows) is decoded in one pass, so
-// a tile's few rows share the pass's start-up and its partial last MFMA
-// tile with its neighbour.  A planned tile's per-lane state waits in LDS
-// until its gather, so no two tiles' state is live in registers.
+// Batched decode (every method but the full filter, no C / C+ fallback).  A
+// wave plans up to kBatchSlots tiles, each tile's rows behind the last one's
+// (at most 256 rows), decodes them in one pass and gathers the tiles, so the
+// pass's start-up and its partial last MFMA tile are shared.  A planned
+// tile's per-lane state waits in LDS until its gather, so no two tiles' state
+// is live in registers.
 // ---------------------------------------------------------------------------
 
-struct LaneState {
-    float s, t;       // footprint position
-    uint32_t idx;     // gi | gd << 16: tap (i, j) at item gi + i + gd j (via the rank table for Mask/List)
-    uint32_t misc;    // draw_row | exact << 8 | draws << 9 | in_screen << 10
-};
+constexpr int kBatchSlots = 4;
 
-struct BatchLds {
-    DecLds L;                   // vals, rows (the batch), keys (sort keys, then the staging rows), rank (slot 0), bytes
-    uint8_t rank1[256];         // rank table of slot 1
-    LaneState st[2][kWave];     // per-lane state by slot
-};
-
-struct Pending {
-    int tx, ty;
-    int base;                   // first row of the tile in the batch
-};
-
-// Plan one tile: decisions, staging rows (L.keys as int2), the rank table
-// and per-lane state of `slot`, debug outputs, tile record and counters.
-// Returns the tile's row count.
-// The rows go behind the batch's rows (from row `base`) when they fit there,
-// else to the staging area (L.keys) for the caller to move after a flush.
-template <int METHOD, bool STATS>
-__device__ __forceinline__ int plan_tile(const FilterArgs& a, BatchLds& BL, int slot, int base, int64_t tile, int tx,
-                                         int ty, const Footprint& f, FrameCounters& fc)
+template <int METHOD, bool FB>
+constexpr bool batched()
 {
-    DecLds& L = BL.L;
-    int2* const stage = reinterpret_cast<int2*>(L.keys);
-    uint8_t* const rank = slot ? BL.rank1 : L.rank;
+    return !FB && METHOD != CTF_BILINEAR4;
+}
+
+// Per wave.  vals (and for the bicubic List past 16x16 rows and more, on an
+// empty batch) also serves as the sort buffer: no value is live while a tile
+// is planned.
+template <int F>
+struct BatchLds {
+    float4 vals[kMaxItems];               // decoded texels, by row
+    int2 rows[kMaxItems];                 // texel coordinates to decode
+    uint64_t more[F == 4 ? kMaxItems : 1];
+    uint32_t window[kWindowWords];        // window_set
+    uint8_t rank[256];                    // position of the window -> item
+    float2 st[kBatchSlots][kWave];        // footprint position of the lane
+    uint32_t item[kBatchSlots][kWave];    // F = 2: items of the two footprint rows, draw row and flags; F = 4: items
+    uint32_t draw[F == 4 ? kBatchSlots : 1][F == 4 ? kWave : 1];   // F = 4: draw row and flags
+    int4 info[kBatchSlots];               // tile x, y, first row, whether wholly on screen
+};
+static_assert(offsetof(BatchLds<4>, rows) == 16 * kMaxItems && offsetof(BatchLds<4>, more) == 24 * kMaxItems,
+              "sort buffer layout");
+
+// Per-lane flags over the draw row.
+constexpr uint32_t kExact = 1u << 15, kDraws = 1u << 14;
+
+// Plan one tile on the batch's rows from `base`: decisions, rows, per-lane
+// state of `slot`, debug outputs, tile record and counters.  Returns the
+// tile's row count, or -1, with nothing written, if the tile needs an empty
+// batch (its rows do not fit behind the others, or it sorts).
+template <int METHOD, bool STATS, int FILTER>
+__device__ __forceinline__ int plan_tile(const FilterArgs& a, BatchLds<Taps<FILTER>::F>& BL, int slot, int base,
+                                         int64_t tile, int tx, int ty, const WaveFootprint& f, FrameCounters& fc)
+{
+    constexpr int F = Taps<FILTER>::F, O = Taps<FILTER>::O;
+    constexpr bool kCollab = collaborative(METHOD);
+    constexpr bool kWindowed = METHOD == CTF_LIST || METHOD == CTF_MASK;
+    uint64_t* const keys = reinterpret_cast<uint64_t*>(BL.vals);
     const int lane = lane_id();
-    const int px = tx * kTile + (lane & 7), py = ty * kTile + (lane >> 3);
-    const bool in_screen = lane_on_screen(a, tx, ty);
-    const bool inA = f.active && f.magnify;
-    const uint64_t act = ballot(f.active);
-    const uint64_t A = ballot(inA);
+    const bool inside = tile_interior(a, tx, ty);
+    const uint64_t act = f.act, A = f.A;
     const int nA = popc64(A);
+    const int ox = f.x0 - O, oy = f.y0 - O;   // upper-left tap of the FxF footprint
 
     int xmin = 0, ymin = 0, bbw = 0, bbh = 0;
-    constexpr bool kCollab = METHOD == CTF_LIST || METHOD == CTF_BOX || METHOD == CTF_MASK;
     // Mask and List only need a 16x16 window that holds every footprint of
     // A: try the one centred on a lane of A (lane 36 when it is in A) before
-    // reducing the exact box.  Bit positions are relative to the window's
-    // corner; the texels, their order and every decision are the same.
+    // reducing the exact box.  Positions are relative to the window's corner;
+    // the texels, their order and every decision are the same.
     bool window = false;
-    if constexpr ((METHOD == CTF_LIST || METHOD == CTF_MASK) && !STATS) {
-        if (nA > 0) {
+    if constexpr (kWindowed && !STATS) {
+        if (A) {
             const int rl = ((A >> 36) & 1ull) ? 36 : (int)__builtin_ctzll(A);
-            const int ox = __builtin_amdgcn_readlane(f.x0, rl) - 7, oy = __builtin_amdgcn_readlane(f.y0, rl) - 7;
-            const bool outside =
-                inA && ((uint32_t)f.x0 - (uint32_t)ox > 14u || (uint32_t)f.y0 - (uint32_t)oy > 14u);
-            if (ballot(outside) == 0) {
-                window = true;
-                xmin = ox;
-                ymin = oy;
-            }
+            xmin = __builtin_amdgcn_readlane(ox, rl) - (16 - F) / 2;
+            ymin = __builtin_amdgcn_readlane(oy, rl) - (16 - F) / 2;
+            const uint32_t dx = (uint32_t)ox - (uint32_t)xmin, dy = (uint32_t)oy - (uint32_t)ymin;
+            window = (ballot((dx > dy ? dx : dy) > (uint32_t)(16 - F)) & A) == 0;
         }
     }
-    if ((kCollab || STATS) && nA > 0 && !window) {
-        xmin = wave_min(inA ? f.x0 : INT32_MAX);
-        ymin = wave_min(inA ? f.y0 : INT32_MAX);
-        bbw = wave_max(inA ? f.x0 + 1 : INT32_MIN) - xmin + 1;
-        bbh = wave_max(inA ? f.y0 + 1 : INT32_MIN) - ymin + 1;
+    if ((kCollab || STATS) && A && !window) {
+        const bool inA = lane_in(A);
+        xmin = wave_min(inA ? ox : INT32_MAX);
+        ymin = wave_min(inA ? oy : INT32_MAX);
+        bbw = wave_max(inA ? ox + F - 1 : INT32_MIN) - xmin + 1;
+        bbh = wave_max(inA ? oy + F - 1 : INT32_MIN) - ymin + 1;
     }
-    const bool fits16 = window || (nA > 0 && bbw <= 16 && bbh <= 16);
+    const bool fits16 = window || (A && bbw <= 16 && bbh <= 16);
+    if constexpr (F == 4 && (METHOD == CTF_LIST || STATS)) {
+        if (A && !fits16 && base > 0) return -1;   // the sort buffer covers the rows
+    }
 
-    uint64_t B[4] = {0, 0, 0, 0};
-    int nmask = 0;
-    constexpr bool kNeedMask = METHOD == CTF_MASK || METHOD == CTF_LIST || STATS;
-    if (kNeedMask && fits16) {
-        reinterpret_cast<uint32_t*>(L.bytes)[lane] = 0u;
-        wave_lds_sync();
-        if (inA) L.bytes[16 * (f.y0 - ymin) + (f.x0 - xmin)] = 1;
-        wave_lds_sync();
-        uint64_t C[4];
+    const int corner = lane_in(A) ? 16 * (oy - ymin) + (ox - xmin) : 0;
+    WindowSet S{0u, 0u, 0};
+    uint64_t B[4] = {0, 0, 0, 0};   // tile records only
+    if ((kWindowed || STATS) && fits16) {
+        S = window_set<F>(BL.window, lane_in(A), corner);
+        if constexpr (STATS) {
+            const uint8_t* bytes = reinterpret_cast<const uint8_t*>(BL.window + kWindowPad);
+            uint64_t C[4];
 #pragma unroll
-        for (int w = 0; w < 4; ++w) C[w] = ballot(L.bytes[64 * w + lane] != 0);
-        footprint_mask(C, B);
-        nmask = popc64(B[0]) + popc64(B[1]) + popc64(B[2]) + popc64(B[3]);
+            for (int w = 0; w < 4; ++w) C[w] = ballot(bytes[64 * w + lane] != 0);
+            footprint_mask_f<F>(C, B);
+        }
     }
 
     const int k = a.max_evals;
     int n = 0;
     bool cap_ok = true, count_ok = true, success = false, sorted = false;
-    int unique = nmask;
+    int unique = S.n;
     if constexpr (METHOD == CTF_BOX) {
         const int64_t area = (int64_t)bbw * bbh;
         n = area > INT32_MAX ? INT32_MAX : (int)area;
@@ -759,131 +780,103 @@ __device__ __forceinline__ int plan_tile(const FilterArgs& a, BatchLds& BL, int 
         success = nA > 0 && cap_ok && count_ok;
     } else if constexpr (METHOD == CTF_MASK) {
         cap_ok = fits16;
-        n = fits16 ? nmask : 0;
+        n = S.n;
         count_ok = n <= k * nA;
         success = fits16 && count_ok;
     } else if constexpr (METHOD == CTF_LIST) {
-        if (nA > 0 && !fits16) {
-            n = dec_list_sorted<2>(L, inA, f.x0, f.y0, xmin, ymin);
+        n = S.n;
+        if (A && !fits16) {
+            n = dec_list_sorted<F>(keys, lane_in(A), ox, oy, xmin, ymin);
             sorted = true;
-        } else {
-            n = nmask;
         }
         unique = n;
         count_ok = n <= k * nA;
         success = nA > 0 && count_ok;
     }
     if constexpr (STATS && METHOD != CTF_LIST) {
-        if (nA > 0 && !fits16) unique = dec_list_sorted<2>(L, inA, f.x0, f.y0, xmin, ymin);
+        if (A && !fits16) unique = dec_list_sorted<F>(keys, lane_in(A), ox, oy, xmin, ymin);
     }
     if (nA == 0) unique = 0;
 
-    bool exact, draws;
-    if constexpr (METHOD == CTF_BILINEAR4) {
-        exact = f.active;
-        draws = false;
-    } else if constexpr (METHOD == CTF_STF1) {
-        exact = false;
-        draws = f.active;
-    } else {
-        exact = inA && success;
-        draws = f.active && !exact;
-    }
-    const uint64_t stfmask = ballot(draws);
+    // lanes filtered exactly; the other active lanes draw one texel
+    const uint64_t exact = kCollab && success ? A : 0ull;
+    const uint64_t stfmask = act & ~exact;
     const int nstf = popc64(stfmask);
+    const int ns = success ? n : 0;
+    const int R = ns + nstf;
+    if (base + R > kMaxItems) return -1;
     int2 pick = make_int2(INT32_MIN, INT32_MIN);
-    if (draws) {
+    int2* const dst = BL.rows + base;
+    const int draw_row = ns + mbcnt(stfmask);
+    if (lane_in(stfmask)) {
         uint32_t h1, h2;
-        stf_hashes(a.seed, a.layer, px, py, h1, h2);
-        pick = stf_pick_h(f, h1, h2);
+        stf_hashes(a.seed, a.layer, tx * kTile + (lane & 7), ty * kTile + (lane >> 3), h1, h2);
+        Footprint g;
+        g.x0 = f.x0;
+        g.y0 = f.y0;
+        g.s = f.s;
+        g.t = f.t;
+        pick = stf_pick_filter<FILTER>(g, h1, h2);
+        dst[draw_row] = pick;
     }
 
-    // rows (behind the batch or in the staging area) and the inverse table
-    // of Mask/List.  Only the first tap of each footprint row is looked up
-    // at gather time: in a row-major list the texel right of a footprint
-    // texel is the next item.
-    const int rank_act = mbcnt(act);
-    const int ns = success ? n : 0;
-    int R;
-    if constexpr (METHOD == CTF_BILINEAR4) {
-        R = 4 * popc64(act);
-        int2* const dst = base + R <= kMaxItems ? L.rows + base : stage;
-        if (f.active) {
+    // rows and the items of this lane's footprint rows (their first taps: in
+    // a row-major list the texel right of a footprint texel is the next item)
+    int item[F];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) dst[4 * rank_act + q] = make_int2(f.x0 + (q & 1), f.y0 + (q >> 1));
+    for (int r = 0; r < F; ++r) item[r] = 0;
+    auto list_out = [&](int i, int2 c) {
+        if (STATS && a.lists) reinterpret_cast<int2*>(a.lists)[(size_t)tile * kMaxItems + i] = c;
+    };
+    if (success) {
+        if (METHOD == CTF_BOX || sorted) {
+            for (int i = lane; i < ns; i += kWave) {
+                int2 c;
+                if (METHOD == CTF_BOX) {
+                    c = make_int2(xmin + i % bbw, ymin + i / bbw);
+                } else {
+                    const uint64_t key = keys[i];
+                    c = make_int2(xmin + (int)(uint32_t)key, ymin + (int)(key >> 32));
+                }
+                dst[i] = c;
+                list_out(i, c);
+            }
+            if (METHOD == CTF_BOX) {
+#pragma unroll
+                for (int r = 0; r < F; ++r) item[r] = (ox - xmin) + (oy + r - ymin) * bbw;
+            } else if (lane_in(A)) {
+#pragma unroll
+                for (int r = 0; r < F; ++r)
+                    item[r] = dec_list_find(keys, n, ((uint64_t)(uint32_t)(oy + r - ymin) << 32) | (uint32_t)(ox - xmin));
+            }
+        } else {
+            reinterpret_cast<uint32_t*>(BL.rank)[lane] = S.ranks;
+            const int cx = xmin + 4 * (lane & 3), cy = ymin + (lane >> 2);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (S.set & (1u << (8 * q))) {
+                    const int r = (int)((S.ranks >> (8 * q)) & 0xffu);
+                    dst[r] = make_int2(cx + q, cy);
+                    list_out(r, make_int2(cx + q, cy));
+                }
+            }
+            wave_lds_sync();
+#pragma unroll
+            for (int r = 0; r < F; ++r) item[r] = BL.rank[(corner + 16 * r) & 0xff];
         }
+    }
+    if (a.stf_xy && (inside || lane_on_screen(a, tx, ty)))
+        reinterpret_cast<int2*>(a.stf_xy)[tile_pixel0(a, tx, ty) + lane_pixel(a)] = pick;
+    BL.st[slot][lane] = make_float2(f.s, f.t);
+    const uint32_t misc = (uint32_t)(draw_row & 0xff) | (lane_in(exact) ? kExact : 0u) | (lane_in(stfmask) ? kDraws : 0u);
+    if constexpr (F == 2) {
+        BL.item[slot][lane] = (uint32_t)(item[0] & 0xff) | (uint32_t)(item[1] & 0xff) << 8 | misc << 16;
     } else {
-        R = ns + nstf;
-        int2* const dst = base + R <= kMaxItems ? L.rows + base : stage;
-        if (success) {
-            if (sorted) {
-                // the lane's item indices first (they read the sorted keys);
-                // in place when the rows go to the staging area
-                if (inA) {
-#pragma unroll
-                    for (int q = 0; q < 4; q += 2) {
-                        const uint64_t key = ((uint64_t)(uint32_t)(f.y0 + (q >> 1) - ymin) << 32) |
-                                             (uint32_t)(f.x0 - xmin);
-                        rank[4 * lane + q] = (uint8_t)dec_list_find(L.keys, n, key);
-                    }
-                }
-                wave_lds_sync();
-            }
-            if (METHOD == CTF_BOX || sorted) {
-                for (int i = lane; i < ns; i += kWave) {
-                    int ex, ey;
-                    if (METHOD == CTF_BOX) {
-                        ex = xmin + i % bbw;
-                        ey = ymin + i / bbw;
-                    } else {
-                        const uint64_t key = L.keys[i];
-                        ex = xmin + (int)(uint32_t)key;
-                        ey = ymin + (int)(key >> 32);
-                    }
-                    dst[i] = make_int2(ex, ey);
-                    if (STATS && a.lists) reinterpret_cast<int2*>(a.lists)[(size_t)tile * kMaxItems + i] = make_int2(ex, ey);
-                }
-            } else {
-                // bit `lane` of word w is position 64 w + lane of the window:
-                // column lane % 16, row 4 w + lane / 16
-                const int cx = xmin + (lane & 15);
-                int cy = ymin + (lane >> 4), first = 0;
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    if ((B[w] >> lane) & 1u) {
-                        const int r = first + mbcnt(B[w]);
-                        rank[64 * w + lane] = (uint8_t)r;
-                        dst[r] = make_int2(cx, cy);
-                        if (STATS && a.lists) reinterpret_cast<int2*>(a.lists)[(size_t)tile * kMaxItems + r] = make_int2(cx, cy);
-                    }
-                    first += popc64(B[w]);
-                    cy += 4;
-                }
-            }
-        }
-        if (draws) dst[ns + mbcnt(stfmask)] = pick;
+        BL.item[slot][lane] = (uint32_t)(item[0] & 0xff) | (uint32_t)(item[1] & 0xff) << 8 |
+                              (uint32_t)(item[2] & 0xff) << 16 | (uint32_t)(item[3] & 0xff) << 24;
+        BL.draw[slot][lane] = misc;
     }
-    if (in_screen && a.stf_xy)
-        reinterpret_cast<int2*>(a.stf_xy)[tile_pixel0(a, tx, ty) + lane_pixel(a)] =
-            draws ? pick : make_int2(INT32_MIN, INT32_MIN);
-    int gi = 0, gd = 0;
-    if constexpr (METHOD == CTF_BILINEAR4) {
-        gi = 4 * rank_act;
-        gd = 2;
-    } else if constexpr (METHOD == CTF_BOX) {
-        gi = (f.x0 - xmin) + (f.y0 - ymin) * bbw;
-        gd = bbw;
-    } else if constexpr (METHOD == CTF_LIST || METHOD == CTF_MASK) {
-        gi = sorted ? 4 * lane : 16 * (f.y0 - ymin) + (f.x0 - xmin);
-        gd = sorted ? 2 : 16;
-    }
-    LaneState ls;
-    ls.s = f.s;
-    ls.t = f.t;
-    ls.idx = (uint32_t)(gi & 0xffff) | ((uint32_t)(gd & 0xffff) << 16);
-    ls.misc = (uint32_t)((ns + mbcnt(stfmask)) & 0xff) | (exact ? 1u << 8 : 0u) | (draws ? 1u << 9 : 0u) |
-              (in_screen ? 1u << 10 : 0u);
-    BL.st[slot][lane] = ls;
+    if (lane == 0) BL.info[slot] = make_int4(tx, ty, base, inside ? 1 : 0);
     if (STATS && lane == 0 && a.tile_stats)
         write_tile_stats(a, tile, act, A, stfmask, fits16, B, xmin, ymin, bbw, bbh, n, unique, R, success, cap_ok,
                          count_ok, nA);
@@ -892,91 +885,112 @@ __device__ __forceinline__ int plan_tile(const FilterArgs& a, BatchLds& BL, int 
 }
 
 // Gather and weight a decoded tile from its per-lane state.
-template <int METHOD>
-__device__ __forceinline__ void gather_tile(const FilterArgs& a, BatchLds& BL, int slot, const Pending& pd)
+template <int METHOD, int FILTER>
+__device__ __forceinline__ void gather_tile(const FilterArgs& a, const BatchLds<Taps<FILTER>::F>& BL, int slot)
 {
+    constexpr int F = Taps<FILTER>::F;
     const int lane = lane_id();
-    const LaneState ls = BL.st[slot][lane];
-    const uint8_t* const rank = slot ? BL.rank1 : BL.L.rank;
-    const float4* const vals = BL.L.vals + pd.base;
-    const int gi = (int)(ls.idx & 0xffff), gd = (int)(ls.idx >> 16);
-    const bool exact = (ls.misc >> 8) & 1u, draws = (ls.misc >> 9) & 1u, in_screen = (ls.misc >> 10) & 1u;
+    const int4 info = BL.info[slot];
+    const float2 st = BL.st[slot][lane];
+    const uint32_t item = BL.item[slot][lane];
+    const uint32_t misc = F == 2 ? item >> 16 : BL.draw[F == 4 ? slot : 0][F == 4 ? lane : 0];
+    const int tx = __builtin_amdgcn_readfirstlane(info.x), ty = __builtin_amdgcn_readfirstlane(info.y);
+    const float4* const vals = BL.vals + __builtin_amdgcn_readfirstlane(info.z);
     float4 res = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (draws) res = vals[ls.misc & 0xff];
-    if (exact) {
-        // each footprint row is two consecutive items
-        int i0 = gi, i2 = gi + gd;
-        if constexpr (METHOD == CTF_LIST || METHOD == CTF_MASK) {
-            i0 = rank[i0];
-            i2 = rank[i2];
+    if (misc & kDraws) res = vals[misc & 0xff];
+    if (collaborative(METHOD) && (misc & kExact)) {
+        if constexpr (F == 2) {
+            const int i0 = item & 0xff, i1 = (item >> 8) & 0xff;
+            res = bilerp(st.x, st.y, vals[i0], vals[i0 + 1], vals[i1], vals[i1 + 1]);
+        } else {
+            float wx[4], wy[4];
+            taps32<FILTER>(st.x, wx);
+            taps32<FILTER>(st.y, wy);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float4* const v = vals + ((item >> (8 * r)) & 0xff);
+                res = col_acc(wy[r], row4(wx, v[0], v[1], v[2], v[3]), res, r == 0);
+            }
         }
-        res = bilerp(ls.s, ls.t, vals[i0], vals[i0 + 1], vals[i2], vals[i2 + 1]);
     }
-    if (in_screen) {
-        char* const ob = reinterpret_cast<char*>(reinterpret_cast<float4*>(a.out) + tile_pixel0(a, pd.tx, pd.ty));
+    if (__builtin_amdgcn_readfirstlane(info.w) || lane_on_screen(a, tx, ty)) {
+        char* const ob = reinterpret_cast<char*>(reinterpret_cast<float4*>(a.out) + tile_pixel0(a, tx, ty));
         *reinterpret_cast<float4*>(ob + lane_pixel(a) * 16u) = res;
     }
 }
 
-// The batch of planned tiles of one wave (slots 0 and 1, named so that no
-// private array is indexed at run time).
-struct Batch {
-    Pending p0{}, p1{};
-    int npend = 0, rows = 0;
-};
-
-// Decode the batch and gather its tiles in slot order.
-template <int METHOD, int P>
-__device__ __forceinline__ void batch_flush(const FilterArgs& a, BatchLds& BL, Batch& bt, const InferGrid& G,
-                                            const FwdWeights<P>& W, const Biases& Bz, FrameCounters& fc)
+// The wave's share of one layer: plan, decode and gather its tiles in
+// batches.  foot(uv, d) is the lanes' footprint in the layer's coordinates.
+template <int METHOD, int P, bool STATS, int FILTER, class Foot>
+__device__ __forceinline__ void batch_walk(const FilterArgs& a, BatchLds<Taps<FILTER>::F>& BL, const InferGrid& G,
+                                           const FwdWeights<P>& W, const Biases& Bz, const Band& band,
+                                           FrameCounters& fc, Foot&& foot)
 {
-    const int lane = lane_id();
-    wave_lds_sync();
-    decode_rows<P>(BL.L, bt.rows, G, W, Bz, lane & 15, lane >> 4);
-    wave_lds_sync();
-    if (bt.npend >= 1) gather_tile<METHOD>(a, BL, 0, bt.p0);
-    if (bt.npend == 2) gather_tile<METHOD>(a, BL, 1, bt.p1);
-    fc.rows += (uint32_t)((bt.rows + 15) & ~15);
-    bt.npend = 0;
-    bt.rows = 0;
-    wave_lds_sync();
-}
-
-// Plan a tile and append its rows to the batch (decoding the batch first
-// when the rows do not fit behind it).  The caller decodes a full batch (two
-// tiles) before calling.
-template <int METHOD, int P, bool STATS>
-__device__ __forceinline__ void batch_add(const FilterArgs& a, BatchLds& BL, Batch& bt, const InferGrid& G,
-                                          const FwdWeights<P>& W, const Biases& Bz, FrameCounters& fc,
-                                          const StripWalk& cur, const Footprint& f)
-{
-    const int lane = lane_id();
-    const int R = plan_tile<METHOD, STATS>(a, BL, bt.npend, bt.rows, cur.tile, cur.tx, cur.ty, f, fc);
-    if (bt.rows + R > kMaxItems) {
-        // planned into slot 1 with its rows staged: decode slot 0, then move
-        // the state, the table and the rows
-        batch_flush<METHOD, P>(a, BL, bt, G, W, Bz, fc);
-        BL.st[0][lane] = BL.st[1][lane];
-        reinterpret_cast<uint32_t*>(BL.L.rank)[lane] = reinterpret_cast<const uint32_t*>(BL.rank1)[lane];
-        const int2* stage = reinterpret_cast<const int2*>(BL.L.keys);
-        for (int i = lane; i < R; i += kWave) BL.L.rows[i] = stage[i];
+    // (the tile record's sorts run on an empty batch)
+    constexpr int kSlots = STATS ? 1 : kBatchSlots;
+    int npend = 0, rows = 0, last = 0;
+    bool redo = false;
+    StripWalk next(band, a.ntiles, a.tiles_x);
+    float2 uv_next;
+    float4 d_next;
+    load_tile_px_s(a, next, band.end, uv_next, d_next);
+    for (;;) {
+        // The next tile's inputs were requested before the last tile was
+        // planned: wait for them here, before the gather's stores, which
+        // complete in order with them.
+        settle(uv_next, d_next);
+        const bool more = next.tile < band.end;
+        // a batch is full when no slot is left or a tile like the last one
+        // would not fit (plan_tile has the final word)
+        if (npend && (!more || redo || npend == kSlots || rows + last > kMaxItems)) {
+            wave_lds_sync();
+            decode_rows<P>(BL.rows, BL.vals, rows, G, W, Bz);
+            wave_lds_sync();
+            for (int i = 0; i < npend; ++i) gather_tile<METHOD, FILTER>(a, BL, i);
+            fc.rows += (uint32_t)((rows + 15) & ~15);
+            npend = 0;
+            rows = 0;
+            wave_lds_sync();
+        }
+        if (!more) break;
+        float2 uv = uv_next;
+        float4 d = d_next;
+        // (copies made here: otherwise the next request goes to other
+        // registers and is waited for at once, to be moved into these)
+        asm volatile("" : "+v"(uv.x), "+v"(uv.y), "+v"(d.x), "+v"(d.y), "+v"(d.z), "+v"(d.w));
+        const StripWalk cur = next;
+        next.advance();
+        load_tile_px_s(a, next, band.end, uv_next, d_next);
+        const WaveFootprint f = foot(uv, d);
+        const int R = plan_tile<METHOD, STATS, FILTER>(a, BL, npend, rows, cur.tile, cur.tx, cur.ty, f, fc);
+        redo = R < 0;
+        if (redo) {
+            next = cur;
+            load_tile_px_s(a, next, band.end, uv_next, d_next);
+        } else {
+            ++npend;
+            rows += R;
+            last = R;
+        }
     }
-    wave_lds_sync();   // the next plan rewrites the keys
-    Pending& pd = bt.npend ? bt.p1 : bt.p0;
-    pd.tx = cur.tx;
-    pd.ty = cur.ty;
-    pd.base = bt.rows;
-    ++bt.npend;
-    bt.rows += R;
 }
 
-template <int METHOD, int P, bool STATS>
+template <int F>
+__device__ __forceinline__ void batch_init(BatchLds<F>& BL)
+{
+    if (lane_id() < kWindowPad) BL.window[lane_id()] = 0u;
+    wave_lds_sync();
+}
+
+template <int METHOD, int P, bool STATS, int FILTER>
 __global__ __launch_bounds__(64 * kDecWaves, 3) void k_filter_dec_batch(FilterArgs a, DevDecoderWeights D)
 {
-    __shared__ BatchLds lds_all[kDecWaves];
+    constexpr int F = Taps<FILTER>::F;
+    __shared__ BatchLds<F> lds_all[kDecWaves];
     const int wid = wave_in_block();
     const int lane = lane_id();
-    BatchLds& BL = lds_all[wid];
+    BatchLds<F>& BL = lds_all[wid];
+    batch_init(BL);
     FwdWeights<P> W;
     W.load(D.w, lane);
     Biases Bz;
@@ -984,26 +998,9 @@ __global__ __launch_bounds__(64 * kDecWaves, 3) void k_filter_dec_batch(FilterAr
     const float tex_w = (float)D.grid.tex_w;
     const Band band(a.ntiles, wid);
     FrameCounters fc;
-    Batch bt;
-    float2 uv_next;
-    float4 d_next;
-    StripWalk next(band, a.ntiles, a.tiles_x);
-    load_tile_px_s(a, next, band.end, uv_next, d_next);
-    settle(uv_next, d_next);
-    while (next.tile < band.end) {
-        const StripWalk cur = next;
-        const float2 uv = uv_next;
-        const float4 d = d_next;
-        // decode a full batch first, then request the next tile's inputs:
-        // their latency is hidden by this tile's planning and the next
-        // iteration's decode, and no wait inside the decode covers them
-        if (bt.npend == 2) batch_flush<METHOD, P>(a, BL, bt, D.grid, W, Bz, fc);
-        next.advance();
-        load_tile_px_s(a, next, band.end, uv_next, d_next);
-        const Footprint f = footprint(uv.x, uv.y, d, tex_w, tex_w);
-        batch_add<METHOD, P, STATS>(a, BL, bt, D.grid, W, Bz, fc, cur, f);
-    }
-    if (bt.npend) batch_flush<METHOD, P>(a, BL, bt, D.grid, W, Bz, fc);
+    batch_walk<METHOD, P, STATS, FILTER>(a, BL, D.grid, W, Bz, band, fc, [&](float2 uv, float4 d) {
+        return wave_footprint(uv.x, uv.y, d, tex_w, tex_w);
+    });
     if (lane == 0 && a.frame_stats) fc.flush(a.frame_stats);
 }
 
@@ -1027,8 +1024,6 @@ int64_t resident_blocks(K kernel, int threads, int64_t work_blocks, int64_t min_
     if (blocks > work_blocks) blocks = work_blocks;
     return (blocks + 7) / 8 * 8;
 }
-
-constexpr bool collaborative(int m) { return m == CTF_LIST || m == CTF_BOX || m == CTF_MASK; }
 
 // Instantiation for the call's statistics and fallback flags; waves of a
 // collaborative method carry the C / C+ code only when it is asked for, so
@@ -1054,9 +1049,8 @@ struct GoFilter {
         {
             const int64_t work = (a.ntiles + kDecWaves - 1) / kDecWaves;
             const int64_t least = dec_min_blocks(a.ntiles, a.tiles_x, 1);
-            if constexpr (FILTER == CTF_FILTER_BILINEAR && !FB && METHOD != CTF_BILINEAR4) {
-                // (the 4-tap filter's full tiles of 256 rows never share a batch)
-                auto k = k_filter_dec_batch<METHOD, P, STATS>;
+            if constexpr (batched<METHOD, FB>()) {
+                auto k = k_filter_dec_batch<METHOD, P, STATS, FILTER>;
                 const int64_t blocks = resident_blocks(k, 64 * kDecWaves, work, least);
                 hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(64 * kDecWaves), 0, s, a, d);
             } else {
@@ -1094,23 +1088,39 @@ struct LayerSet {
     int n;
 };
 
+// LDS of one wave of the layered launch.
+template <int METHOD, bool FB, int FILTER>
+struct LayerLds {
+    using Type = DecLds;
+};
+template <int METHOD, int FILTER>
+struct LayerLds<METHOD, false, FILTER> {
+    using Type = std::conditional_t<batched<METHOD, false>(), BatchLds<Taps<FILTER>::F>, DecLds>;
+};
+
 template <int METHOD, int P, bool STATS, bool FB, int FILTER>
 __global__ __launch_bounds__(64 * kDecWaves, (dec_waves_per_simd<METHOD, FILTER>())) void
 k_filter_layers(FilterArgs a, LayerSet LS)
 {
-    __shared__ DecLds lds_all[kDecWaves];
+    using Lds = typename LayerLds<METHOD, FB, FILTER>::Type;
+    __shared__ Lds lds_all[kDecWaves];
     const int wid = wave_in_block();
     const int lane = lane_id();
-    DecLds& L = lds_all[wid];
+    Lds& L = lds_all[wid];
+    if constexpr (batched<METHOD, FB>()) batch_init(L);
     const Band band(a.ntiles, wid);
     const int64_t npix = (int64_t)a.sw * a.sh;
     FrameCounters fc;
     for (int l = 0; l < LS.n; ++l) {
         const DevDecoderWeights& D = LS.dec[l];
+        // (opaque, so that the lane's weight offsets are not kept in registers
+        // across the tile walk for the next layer)
+        int wl = lane;
+        asm volatile("" : "+v"(wl));
         FwdWeights<P> W;
-        W.load(D.w, lane);
+        W.load(D.w, wl);
         Biases Bz;
-        Bz.load(D.bias, lane);
+        Bz.load(D.bias, wl);
         const float tex_w = (float)D.grid.tex_w;
         const float m00 = LS.xf[l][0], m01 = LS.xf[l][1], m10 = LS.xf[l][2], m11 = LS.xf[l][3];
         FilterArgs al = a;
@@ -1119,24 +1129,34 @@ k_filter_layers(FilterArgs a, LayerSet LS)
         al.stf_xy = a.stf_xy ? a.stf_xy + (size_t)l * npix * 2 : nullptr;
         al.lists = nullptr;
         al.layer = (uint32_t)l;
-        float2 uv_next;
-        float4 d_next;
-        StripWalk next(band, a.ntiles, a.tiles_x);
-        load_tile_px(a, next, band.end, uv_next, d_next);
-        settle(uv_next, d_next);
-        while (next.tile < band.end) {
-            const StripWalk cur = next;
-            const float2 uv = uv_next;
-            const float4 d = d_next;
-            // layer coordinates, float32: u' = fma(m01, v, m00 u), v' = fma(m11, v, m10 u)
-            const float lu = __builtin_fmaf(m01, uv.y, m00 * uv.x), lv = __builtin_fmaf(m11, uv.y, m10 * uv.x);
-            const float4 ld = make_float4(__builtin_fmaf(m01, d.y, m00 * d.x), __builtin_fmaf(m11, d.y, m10 * d.x),
-                                          __builtin_fmaf(m01, d.w, m00 * d.z), __builtin_fmaf(m11, d.w, m10 * d.z));
-            const Footprint f = footprint(lu, lv, ld, tex_w, tex_w);
-            dec_tile<METHOD, P, STATS, FB, FILTER>(al, D.grid, W, Bz, L, cur.tile, cur.tx, cur.ty, f, fc, [&] {
-                next.advance();
-                load_tile_px(a, next, band.end, uv_next, d_next);
+        // layer coordinates, float32: u' = fma(m01, v, m00 u), v' = fma(m11, v, m10 u)
+        auto layer_uv = [&](float2 uv) {
+            return make_float2(__builtin_fmaf(m01, uv.y, m00 * uv.x), __builtin_fmaf(m11, uv.y, m10 * uv.x));
+        };
+        auto layer_d = [&](float4 d) {
+            return make_float4(__builtin_fmaf(m01, d.y, m00 * d.x), __builtin_fmaf(m11, d.y, m10 * d.x),
+                               __builtin_fmaf(m01, d.w, m00 * d.z), __builtin_fmaf(m11, d.w, m10 * d.z));
+        };
+        if constexpr (batched<METHOD, FB>()) {
+            batch_walk<METHOD, P, STATS, FILTER>(al, L, D.grid, W, Bz, band, fc, [&](float2 uv, float4 d) {
+                const float2 lu = layer_uv(uv);
+                return wave_footprint(lu.x, lu.y, layer_d(d), tex_w, tex_w);
             });
+        } else {
+            float2 uv_next;
+            float4 d_next;
+            StripWalk next(band, a.ntiles, a.tiles_x);
+            load_tile_px(a, next, band.end, uv_next, d_next);
+            settle(uv_next, d_next);
+            while (next.tile < band.end) {
+                const StripWalk cur = next;
+                const float2 lu = layer_uv(uv_next);
+                const Footprint f = footprint(lu.x, lu.y, layer_d(d_next), tex_w, tex_w);
+                dec_tile<METHOD, P, STATS, FB, FILTER>(al, D.grid, W, Bz, L, cur.tile, cur.tx, cur.ty, f, fc, [&] {
+                    next.advance();
+                    load_tile_px(a, next, band.end, uv_next, d_next);
+                });
+            }
         }
     }
     if (lane == 0 && a.frame_stats) fc.flush(a.frame_stats);

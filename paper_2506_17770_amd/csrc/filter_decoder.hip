@@ -14,8 +14,10 @@ namespace {
 
 using namespace dec;
 
-// rgba[i] = decoder(xy[i]): 16 texels per MFMA tile, persistent waves; the
-// same per-row instruction sequence as the filter's decode.
+// rgba[i] = decoder(xy[i]): 32 texels per pass (two MFMA tiles), persistent
+// waves; the same per-row instruction sequence as the filter's decode.  The
+// coordinates are read two passes ahead and the latents one pass ahead (an
+// index past n reads texel n - 1).
 template <int P>
 __global__ __launch_bounds__(256, 2) void k_decoder_eval(DevDecoderWeights D, const int2* __restrict__ xy,
                                                          int64_t n, float4* __restrict__ out)
@@ -27,17 +29,25 @@ __global__ __launch_bounds__(256, 2) void k_decoder_eval(DevDecoderWeights D, co
     Biases Bz;
     Bz.load(D.bias, lane);
     const int64_t gw = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
-    const InferLane<P> K(D.grid, g);
-    const int64_t ntiles = (n + 15) / 16;
-    for (int64_t t = gw; t < ntiles; t += nw) {
-        const int64_t row = t * 16 + j;
-        const bool valid = row < n;
-        const int2 p = valid ? xy[row] : make_int2(0, 0);
-        InferFetch F;
+    const int64_t step = (int64_t)gridDim.x * (blockDim.x >> 6) * 32;
+    const InferLane<P> K(D.grid, g >= 2);
+    const int64_t last = n - 1;
+    int64_t f = gw * 32 + (lane & 31);
+    int2 p = xy[f < last ? f : last];
+    InferFetch F;
+    infer_fetch<P>(D.grid, K, p.x, p.y, F);
+    f += step;
+    p = xy[f < last ? f : last];
+    for (int64_t r0 = gw * 32; r0 < n; r0 += step) {
+        u16x4 xa, xb;
+        infer_combine<P>(F, K, xa, xb);
         infer_fetch<P>(D.grid, K, p.x, p.y, F);
-        const f4 y = mlp_forward_b<P>(W, Bz, infer_combine<P>(F), nullptr, nullptr);
-        if (g == 0 && valid) out[row] = make_float4(y[0], y[1], y[2], y[3]);
+        f += step;
+        p = xy[f < last ? f : last];
+        const f4 ya = mlp_forward_b<P>(W, Bz, xa, nullptr, nullptr);
+        const f4 yb = mlp_forward_b<P>(W, Bz, xb, nullptr, nullptr);
+        if (g == 0 && r0 + j < n) out[r0 + j] = make_float4(ya[0], ya[1], ya[2], ya[3]);
+        if (g == 0 && r0 + 16 + j < n) out[r0 + 16 + j] = make_float4(yb[0], yb[1], yb[2], yb[3]);
     }
 }
 
@@ -78,7 +88,7 @@ hipError_t ctf_internal_decoder_eval(const ctf_texture_s* t, const int32_t* xy, 
 {
     if (n <= 0) return hipSuccess;
     const DevDecoderWeights& d = t->dec;
-    int64_t blocks = ((n + 15) / 16 + 3) / 4;
+    int64_t blocks = ((n + 31) / 32 + 3) / 4;
     const int64_t cap = (int64_t)device_cus() * 2;
     if (blocks > cap) blocks = cap;
     const int2* p = reinterpret_cast<const int2*>(xy);
