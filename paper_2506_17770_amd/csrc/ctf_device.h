@@ -376,6 +376,99 @@ __device__ __forceinline__ WindowSet window_set(uint32_t* words, bool inA, int c
     return S;
 }
 
+// The distinct texels of footprints that do not fit a window (any box size).
+// A footprint is F row segments of F texels; the segments are sorted by
+// (row, column), and since a row's segments are then met left to right, a
+// segment adds min(F, distance to the one before it) texels to the row-major
+// list and its own texels are the last F so far.  F |A| keys instead of the
+// F^2 |A| texels: for the cubic filters 256 in place of 1024, and shifts in
+// place of the divisions of a general stride (a wave of a B-spline List at
+// 3840x2160 that took this path ran for over 100 us alone at the frame's end).
+template <int F>
+struct SegmentScratch {
+    uint64_t keys[kWave * F];   // group << 60 | dy << 34 | dx << 8 | id, sorted
+    uint16_t ends[kWave * F];   // items up to and including the segment's
+};
+
+// Sorts the wave's segments and counts; group: 0 or 1 (two sets, group 0
+// first).  Returns the number of distinct texels of both groups, n0 that of
+// group 0, and leaves in first[F lane + r] the item (in its group) of the
+// first texel of this lane's row r, valid where the group has at most 256.
+template <int F>
+__device__ __forceinline__ int segment_sort(SegmentScratch<F>& S, uint8_t* first, bool inA, uint32_t group, int ox,
+                                            int oy, int xmin, int ymin, int& n0)
+{
+    constexpr int N = kWave * F;
+    const int lane = lane_id();
+    const uint32_t dx = (uint32_t)ox - (uint32_t)xmin, dy = (uint32_t)oy - (uint32_t)ymin;   // below 2^26
+#pragma unroll 1
+    for (int r = 0; r < F; ++r)
+        S.keys[F * lane + r] = inA ? ((uint64_t)group << 60) | ((uint64_t)(dy + r) << 34) | ((uint64_t)dx << 8) |
+                                         (uint32_t)(F * lane + r)
+                                   : ~0ull;
+#pragma unroll 1
+    for (int size = 2; size <= N; size <<= 1)
+#pragma unroll 1
+        for (int stride = size >> 1; stride > 0; stride >>= 1) {
+            wave_lds_sync();
+#pragma unroll 1
+            for (int p = lane; p < N / 2; p += kWave) {
+                const int i = ((p & -stride) << 1) | (p & (stride - 1));
+                const uint64_t x = S.keys[i], y = S.keys[i + stride];
+                if ((x > y) == ((i & size) == 0)) {
+                    S.keys[i] = y;
+                    S.keys[i + stride] = x;
+                }
+            }
+        }
+    wave_lds_sync();
+    // this lane counts segments F lane .. F lane + F - 1
+    uint64_t prev = lane ? S.keys[F * lane - 1] : ~0ull;
+    int sum = 0, sum0 = 0;
+    uint32_t sums = 0;   // byte r: texels of the lane's segments up to r
+#pragma unroll
+    for (int r = 0; r < F; ++r) {
+        const uint64_t k = S.keys[F * lane + r];
+        if (k != ~0ull) {
+            const uint32_t gap = ((uint32_t)(k >> 8) & 0x3ffffffu) - ((uint32_t)(prev >> 8) & 0x3ffffffu);
+            const int c = (k >> 34) == (prev >> 34) && gap < (uint32_t)F ? (int)gap : F;
+            sum += c;
+            if ((k >> 60) == 0) sum0 += c;
+        }
+        sums |= (uint32_t)sum << (8 * r);
+        prev = k;
+    }
+    const int incl = wave_scan(sum), base = incl - sum;
+    const int n = __builtin_amdgcn_readlane(incl, 63);
+    n0 = __builtin_amdgcn_readlane(wave_scan(sum0), 63);
+#pragma unroll
+    for (int r = 0; r < F; ++r) {
+        const uint64_t k = S.keys[F * lane + r];
+        const int end = base + (int)((sums >> (8 * r)) & 0xffu);
+        S.ends[F * lane + r] = (uint16_t)end;
+        if (k != ~0ull) first[k & 0xffu] = (uint8_t)(end - F - ((k >> 60) ? n0 : 0));
+    }
+    wave_lds_sync();
+    return n;
+}
+
+// Calls emit(item, group, dx, dy) for every distinct texel (items of both
+// groups in one sequence).
+template <int F, class Emit>
+__device__ __forceinline__ void segment_emit(const SegmentScratch<F>& S, Emit&& emit)
+{
+    const int lane = lane_id();
+#pragma unroll 1
+    for (int p = F * lane; p < F * lane + F; ++p) {
+        const uint64_t k = S.keys[p];
+        if (k == ~0ull) continue;
+        const int begin = p ? S.ends[p - 1] : 0, end = S.ends[p];
+        const int dx = (int)((uint32_t)(k >> 8) & 0x3ffffffu) + F - end, dy = (int)((uint32_t)(k >> 34) & 0x3ffffffu);
+#pragma unroll 1
+        for (int i = begin; i < end; ++i) emit(i, (int)(k >> 60), dx + i, dy);
+    }
+}
+
 // A wave's walk over tiles t0, t0 + step, ... of a row-major tile grid,
 // keeping (tx, ty) up to date with scalar adds: one division per wave
 // instead of a 64-bit division per tile.

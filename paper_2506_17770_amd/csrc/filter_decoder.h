@@ -10,10 +10,10 @@
 // dense MLP pass over the wave's distinct texels.
 //
 // Waves are persistent: each loads the MLP weights into registers once and
-// walks its share of the tiles.  Workgroups are dispatched round-robin over
-// the 8 XCDs; XCD x takes every eighth strip of two tile rows (Band), so
-// that the latent-grid reads of neighbouring tiles share an L2 while every
-// XCD gets a like share of the frame's work.
+// takes tiles from its workgroup's share until it is used up (TileQueue).
+// Workgroups are dispatched round-robin over the 8 XCDs; XCD x takes every
+// eighth strip of two tile rows, so that the latent-grid reads of neighbouring
+// tiles share an L2 while every XCD gets a like share of the frame's work.
 //
 // Instantiated per reconstruction filter (FxF footprints, F = 2 or 4): the
 // bilinear kernels in filter_decoder.hip, the bicubic ones in
@@ -33,93 +33,20 @@ namespace ctf {
 
 namespace dec {
 
-constexpr int kDecWaves = 4;
+// Waves of a workgroup: a whole CU's worth (three per SIMD, the occupancy the
+// kernels' registers allow) on a large frame, four on a small one
+// (dec_launch).  Each wave has a slice of the dynamic LDS behind the queues.
+constexpr int kDecWavesMax = 12, kDecWavesMin = 4;
 
 constexpr bool collaborative(int m) { return m == CTF_LIST || m == CTF_BOX || m == CTF_MASK; }
 
-// vals, rows and keys are contiguous: the bicubic List sort uses the three
-// as one 1024-key buffer before any row or value exists.
 struct DecLds {
-    float4 vals[kMaxItems];     // decoded texels, by row
+    float4 vals[kMaxItems];     // decoded texels, by row; the List's sort before any row is decoded
     int2 rows[kMaxItems];       // texel coordinates to decode
-    uint64_t keys[kMaxItems];   // List past 16x16 (bilinear): sorted unique keys
-    uint8_t rank[256];          // Mask/List: position t -> row (h^-1)
+    uint64_t keys[kMaxItems];   // fallback planning
+    uint8_t rank[256];          // Mask/List: position t -> row (h^-1); List past 16x16: first item of a lane's rows
     uint8_t bytes[256];         // footprint-corner scatter before the ballots
 };
-static_assert(offsetof(DecLds, rows) == 16 * kMaxItems && offsetof(DecLds, keys) == 24 * kMaxItems,
-              "sort buffer layout");
-
-// Sort buffer of the List past 16x16: F^2 keys per lane.
-template <int F>
-__device__ __forceinline__ uint64_t* dec_keys(DecLds& L)
-{
-    if constexpr (F == 2) return L.keys;
-    else return reinterpret_cast<uint64_t*>(&L);
-}
-
-// Exact set of the wave's texels as sorted unique keys (any box size): a
-// bitonic sort of the F^2 |A| footprint keys, then compaction of the first
-// key of every run (rolled loops: few waves take this path, and unrolled it
-// costs the common path registers).  Returns n = |U|; keys[0..n) hold U in (y, x) order (keys:
-// F^2 x 64 entries).
-template <int F>
-__device__ __forceinline__ int dec_list_sorted(uint64_t* keys, bool inA, int ox, int oy, int xmin, int ymin)
-{
-    constexpr int N = kWave * F * F;
-    const int lane = lane_id();
-#pragma unroll 1
-    for (int q = 0; q < F * F; ++q) {
-        uint64_t key = ~0ull;
-        if (inA)
-            key = ((uint64_t)(uint32_t)(oy + q / F - ymin) << 32) | (uint32_t)(ox + q % F - xmin);
-        keys[F * F * lane + q] = key;
-    }
-#pragma unroll 1
-    for (int size = 2; size <= N; size <<= 1)
-#pragma unroll 1
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            wave_lds_sync();
-#pragma unroll 1
-            for (int h = 0; h < N / (2 * kWave); ++h) {
-                const int p = lane + kWave * h;
-                const int i = (p / stride) * stride * 2 + (p % stride);
-                const int j = i + stride;
-                const bool up = (i & size) == 0;
-                const uint64_t x = keys[i], y = keys[j];
-                if ((x > y) == up) {
-                    keys[i] = y;
-                    keys[j] = x;
-                }
-            }
-        }
-    // compaction in rounds of 64 keys: a write index never passes the read
-    // index, and round r writes below every key of the later rounds
-    int base = 0;
-#pragma unroll 1
-    for (int c = 0; c < F * F; ++c) {
-        wave_lds_sync();
-        const int i = kWave * c + lane;
-        const uint64_t k = keys[i];
-        const bool first = k != ~0ull && (i == 0 || keys[i - 1] != k);
-        const uint64_t b = ballot(first);
-        wave_lds_sync();
-        if (first) keys[base + mbcnt(b)] = k;
-        base += popc64(b);
-    }
-    wave_lds_sync();
-    return base;
-}
-
-__device__ __forceinline__ int dec_list_find(const uint64_t* keys, int n, uint64_t key)
-{
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (keys[mid] < key) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
-}
 
 // Rows past R read whatever the row list holds there (the index is kept
 // inside the list): the inference fetch maps any texel to cells inside the
@@ -251,7 +178,8 @@ __device__ __forceinline__ void dec_tile(const FilterArgs& a, const InferGrid& G
     }
 
     const int k = a.max_evals;
-    int n = 0;
+    auto& seg = reinterpret_cast<SegmentScratch<F>&>(L.vals);
+    int n = 0, n0 = 0;
     bool cap_ok = true, count_ok = true, success = false, sorted = false;
     int unique = nmask;
     if constexpr (METHOD == CTF_BOX) {
@@ -267,7 +195,7 @@ __device__ __forceinline__ void dec_tile(const FilterArgs& a, const InferGrid& G
         success = fits16 && count_ok;
     } else if constexpr (METHOD == CTF_LIST) {
         if (nA > 0 && !fits16) {
-            n = dec_list_sorted<F>(dec_keys<F>(L), inA, ox, oy, xmin, ymin);
+            n = segment_sort(seg, L.rank, inA, 0, ox, oy, xmin, ymin, n0);
             sorted = true;
         } else {
             n = nmask;
@@ -277,7 +205,7 @@ __device__ __forceinline__ void dec_tile(const FilterArgs& a, const InferGrid& G
         success = nA > 0 && count_ok;
     }
     if constexpr (STATS && METHOD != CTF_LIST) {
-        if (nA > 0 && !fits16) unique = dec_list_sorted<F>(dec_keys<F>(L), inA, ox, oy, xmin, ymin);
+        if (nA > 0 && !fits16) unique = segment_sort(seg, L.rank, inA, 0, ox, oy, xmin, ymin, n0);
     }
     if (nA == 0) unique = 0;
 
@@ -347,10 +275,6 @@ __device__ __forceinline__ void dec_tile(const FilterArgs& a, const InferGrid& G
     // method's order, then one row per fallback draw) and the inverse table
     // of Mask/List
     const int ns = success ? n : 0;
-    // List past 16x16: per-lane item indices of the F^2 taps, found before
-    // the decode (bilinear: the rank table; bicubic: the keys array, free
-    // once the sorted keys sit at the front of the sort buffer)
-    uint8_t* const sidx = F == 2 ? L.rank : reinterpret_cast<uint8_t*>(L.keys);
     int R;
     if constexpr (METHOD == CTF_BILINEAR4) {
         R = 4 * popc64(act);
@@ -366,20 +290,17 @@ __device__ __forceinline__ void dec_tile(const FilterArgs& a, const InferGrid& G
     } else {
         R = ns + nstf;
         if (success) {
-            if (METHOD == CTF_BOX || sorted) {
-                const uint64_t* keys = dec_keys<F>(L);
+            if (sorted) {
+                segment_emit(seg, [&](int i, int, int dx, int dy) {
+                    L.rows[i] = make_int2(xmin + dx, ymin + dy);
+                    if (STATS && a.lists)
+                        reinterpret_cast<int2*>(a.lists)[(size_t)tile * kMaxItems + i] = make_int2(xmin + dx, ymin + dy);
+                });
+            } else if (METHOD == CTF_BOX) {
                 for (int i = lane; i < ns; i += kWave) {
-                    int ex, ey;
-                    if (METHOD == CTF_BOX) {
-                        ex = xmin + i % bbw;
-                        ey = ymin + i / bbw;
-                    } else {
-                        const uint64_t key = keys[i];
-                        ex = xmin + (int)(uint32_t)key;
-                        ey = ymin + (int)(key >> 32);
-                    }
-                    L.rows[i] = make_int2(ex, ey);
-                    if (STATS && a.lists) reinterpret_cast<int2*>(a.lists)[(size_t)tile * kMaxItems + i] = make_int2(ex, ey);
+                    const int2 c = make_int2(xmin + i % bbw, ymin + i / bbw);
+                    L.rows[i] = c;
+                    if (STATS && a.lists) reinterpret_cast<int2*>(a.lists)[(size_t)tile * kMaxItems + i] = c;
                 }
             } else {
                 // set bit t of B with rank r: row r, and rank[t] = r (h^-1)
@@ -397,15 +318,6 @@ __device__ __forceinline__ void dec_tile(const FilterArgs& a, const InferGrid& G
                     base += popc64(B[w]);
                 }
             }
-            if (sorted && inA) {
-                const uint64_t* keys = dec_keys<F>(L);
-#pragma unroll
-                for (int q = 0; q < F * F; ++q) {
-                    const uint64_t key = ((uint64_t)(uint32_t)(oy + q / F - ymin) << 32) |
-                                         (uint32_t)(ox + q % F - xmin);
-                    sidx[F * F * lane + q] = (uint8_t)dec_list_find(keys, n, key);
-                }
-            }
         }
         if (draws) L.rows[ns + mbcnt(stfmask)] = pick;
     }
@@ -413,15 +325,16 @@ __device__ __forceinline__ void dec_tile(const FilterArgs& a, const InferGrid& G
     // draw is not kept live across it
     if (in_screen && a.stf_xy)
         reinterpret_cast<int2*>(a.stf_xy)[pix] = draws ? pick : make_int2(INT32_MIN, INT32_MIN);
-    // where this lane's taps sit: tap (i, j) has item index gi + i + gd j
-    // (Box: directly; Mask and List: through the table at gi)
+    // where the first tap of this lane's footprint row j sits: gi + gd j (Box:
+    // the item; Mask and List: its place in the table); the row's other taps
+    // are the next items
     int gi = 0, gd = 0;
     if constexpr (METHOD == CTF_BOX) {
         gi = (ox - xmin) + (oy - ymin) * bbw;
         gd = bbw;
     } else if constexpr (METHOD == CTF_LIST || METHOD == CTF_MASK) {
-        gi = sorted ? F * F * lane : 16 * (oy - ymin) + (ox - xmin);
-        gd = sorted ? F : 16;
+        gi = sorted ? F * lane : 16 * (oy - ymin) + (ox - xmin);
+        gd = sorted ? 1 : 16;
     }
     const int draw_row = ns + mbcnt(stfmask);
     wave_lds_sync();
@@ -445,24 +358,21 @@ __device__ __forceinline__ void dec_tile(const FilterArgs& a, const InferGrid& G
     } else {
         if (draws) res = L.vals[draw_row];
         if (kCollab && exact) {
-            const uint8_t* tab = sorted ? sidx : L.rank;
-            auto item = [&](int i, int jj) -> int {
-                const int t = gi + i + gd * jj;
-                if constexpr (METHOD == CTF_BOX) return t;
-                else return tab[t];
+            auto row_item = [&](int jj) -> int {
+                if constexpr (METHOD == CTF_BOX) return gi + gd * jj;
+                else return L.rank[gi + gd * jj];
             };
             if constexpr (F == 2) {
-                res = bilerp(f.s, f.t, L.vals[item(0, 0)], L.vals[item(1, 0)], L.vals[item(0, 1)],
-                             L.vals[item(1, 1)]);
+                const int i0 = row_item(0), i1 = row_item(1);
+                res = bilerp(f.s, f.t, L.vals[i0], L.vals[i0 + 1], L.vals[i1], L.vals[i1 + 1]);
             } else {
                 float wx[4], wy[4];
                 taps32<FILTER>(f.s, wx);
                 taps32<FILTER>(f.t, wy);
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) {
-                    const float4 r = row4(wx, L.vals[item(0, jj)], L.vals[item(1, jj)], L.vals[item(2, jj)],
-                                          L.vals[item(3, jj)]);
-                    res = col_acc(wy[jj], r, res, jj == 0);
+                    const float4* const v = L.vals + row_item(jj);
+                    res = col_acc(wy[jj], row4(wx, v[0], v[1], v[2], v[3]), res, jj == 0);
                 }
             }
         }
@@ -508,100 +418,111 @@ __device__ __forceinline__ bool lane_on_screen(const FilterArgs& a, int tx, int 
     return tx * kTile + (lane & 7) < a.sw && ty * kTile + (lane >> 3) < a.sh;
 }
 
-// XCD-aware share of the tiles for this wave.  Workgroups go round-robin
-// over the 8 XCDs, and XCD x takes the strips of kStripRows tile rows whose
-// index is x mod 8 (neighbouring tile rows, which share latent cells, stay
-// in one XCD's L2).  Contiguous eighths of the screen balance badly: the
-// texels a tile decodes vary down a frame (a minifying region decodes one
-// per pixel), so on a 3840x2160 frame of four planes the costliest eighth
-// decoded twice the rows of the cheapest and its XCD finished last.  The
-// XCD's waves take its tiles in turn (the launch makes the grid a multiple
-// of 8).
+// Tiles of a workgroup, taken one at a time by its waves.
+//
+// The share: workgroups go round-robin over the 8 XCDs, and XCD x owns the
+// strips of kStripRows tile rows whose index is x mod 8 (neighbouring tile
+// rows, which share latent cells, stay in one XCD's L2).  Contiguous eighths
+// of the screen balance badly: the texels a tile decodes vary down a frame (a
+// minifying region decodes one per pixel), so on a 3840x2160 frame of four
+// planes the costliest eighth decoded twice the rows of the cheapest and its
+// XCD finished last.  The XCD's workgroups take runs of 2^run tiles of its
+// rows in turn, left to right.
+//
+// Inside the workgroup the waves draw tiles from an LDS counter.  With a
+// fixed share per wave the SIMD's issue order (oldest wave first) let one
+// wave of a SIMD run ahead of its two neighbours and end early: on a
+// 3840x2160 List frame the waves ended between 88 and 153 us (mean 112) though
+// their rows differ by 4 %, and the frame's last quarter ran with one or two
+// waves per SIMD.  With 12 waves a workgroup fills a CU, so all waves that
+// compete for a SIMD draw from one counter and end together.
 constexpr int kStripLog = 1;   // strips of 2 tile rows
 constexpr int kStripRows = 1 << kStripLog;
 
-struct Band {
-    int64_t end;   // every tile index is below it
-    int lw, nw, xcd;
-    __device__ Band(int64_t ntiles, int wid)
+struct TilePos {
+    int tx, ty;   // ty >= the frame's tile rows: no tile
+};
+
+struct TileQueue {
+    int* counter;   // LDS: next index of the share
+    int tiles_x, tiles_y;
+    uint32_t inv;   // floor((2^32 - 1) / tiles_x)
+    int wg, nwg, xcd, run;
+
+    __device__ __forceinline__ TileQueue(int* c, const FilterArgs& a) : counter(c)
     {
+        tiles_x = a.tiles_x;
+        tiles_y = (int)(a.ntiles / a.tiles_x);
+        inv = 0xffffffffu / (uint32_t)tiles_x;
         xcd = blockIdx.x & 7;
-        lw = (int)(blockIdx.x >> 3) * kDecWaves + wid;
-        nw = (int)(gridDim.x >> 3) * kDecWaves;
-        end = ntiles;
+        wg = blockIdx.x >> 3;
+        nwg = gridDim.x >> 3;
+        // runs of neighbouring tiles share L1 lines; shorter ones where a
+        // share holds few, so that the shares stay even
+        const int64_t share = a.ntiles / gridDim.x;
+        run = share >= 256 ? 3 : share >= 64 ? 2 : 0;
     }
-};
-
-// A wave's walk over its XCD's tiles: the XCD's tile rows in order (row r of
-// the XCD is tile row ((r / kStripRows) * 8 + xcd) * kStripRows + r mod
-// kStripRows), each left to right, every nw-th tile from lw.  Past the last
-// one, tile reads INT64_MAX.
-struct StripWalk {
-    int64_t tile;
-    int tx, ty;
-    int row, xoff, dtx, drow, tiles_x, tiles_y;
-    __device__ __forceinline__ StripWalk(const Band& b, int64_t ntiles, int tiles_x_)
+    __device__ __forceinline__ bool has(TilePos p) const { return p.ty < tiles_y; }
+    // Draws the next index (valid in lane 0 only; place() reads it there).
+    __device__ __forceinline__ int draw() const
     {
-        tiles_x = tiles_x_;
-        tiles_y = (int)(ntiles / tiles_x_);
-        xoff = b.xcd << kStripLog;
-        row = b.lw / tiles_x_;
-        tx = b.lw - row * tiles_x_;
-        drow = b.nw / tiles_x_;
-        dtx = b.nw - drow * tiles_x_;
-        place();
+        int i = 0;
+        if (lane_id() == 0) i = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        return i;
     }
-    __device__ __forceinline__ void place()
+    // Tile of share index i: index n of the XCD, whose row r is tile row
+    // ((r / kStripRows) * 8 + xcd) * kStripRows + r mod kStripRows.  Rows grow
+    // with i, so every index behind one past the frame is past it too.
+    __device__ __forceinline__ TilePos place(int drawn) const
     {
-        ty = (((row >> kStripLog) << (3 + kStripLog)) + xoff) | (row & (kStripRows - 1));
-        tile = ty < tiles_y ? (int64_t)ty * tiles_x + tx : INT64_MAX;
-    }
-    __device__ __forceinline__ void advance()
-    {
-        tx += dtx;
-        row += drow;
-        if (tx >= tiles_x) {
-            tx -= tiles_x;
-            ++row;
+        const uint32_t i = (uint32_t)__builtin_amdgcn_readfirstlane(drawn);
+        const uint32_t n = ((((i >> run) * (uint32_t)nwg + (uint32_t)wg) << run) | (i & ((1u << run) - 1u)));
+        // the quotient estimate is exact or one low for n < 2^31
+        uint32_t r = __umulhi(n, inv), tx = n - r * (uint32_t)tiles_x;
+        if (tx >= (uint32_t)tiles_x) {
+            tx -= (uint32_t)tiles_x;
+            ++r;
         }
-        place();
+        TilePos p;
+        p.tx = (int)tx;
+        p.ty = (int)((((r >> kStripLog) << (3 + kStripLog)) + (uint32_t)(xcd << kStripLog)) | (r & (kStripRows - 1)));
+        return p;
     }
 };
 
-// Workgroups a launch needs so that no wave visits more than
-// kMaxWaveTileVisits tiles over its `layers` walks: an XCD's share of a
-// frame's tiles is at most an eighth plus one strip.
-inline int64_t dec_min_blocks(int64_t ntiles, int tiles_x, int layers)
+// Zeroes a workgroup's queues (one per layer) behind the first tiles, which
+// its waves take by their index; every thread calls this.
+__device__ __forceinline__ void queue_init(int* queues, int layers)
 {
-    return counter_min_blocks((ntiles + (int64_t)8 * kStripRows * tiles_x) * layers, kDecWaves);
+    if ((int)threadIdx.x < layers) queues[threadIdx.x] = (int)(blockDim.x >> 6);
+    __syncthreads();
 }
 
-// Inputs of a tile for this lane, NaN (inactive) outside the band or screen
-// (per-lane 64-bit addresses: the per-tile kernels run faster with these
+// Inputs of a tile for this lane, NaN (inactive) off the screen or without a
+// tile (per-lane 64-bit addresses: the per-tile kernels run faster with these
 // than with load_tile_px_s, measured).
-__device__ __forceinline__ void load_tile_px(const FilterArgs& a, const StripWalk& t, int64_t band_e, float2& uv,
-                                             float4& d)
+__device__ __forceinline__ void load_tile_px(const FilterArgs& a, const TileQueue& q, TilePos t, float2& uv, float4& d)
 {
     const int lane = lane_id();
     uv = make_float2(__builtin_nanf(""), 0.f);
     d = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (t.tile >= band_e) return;
+    if (!q.has(t)) return;
     const int px = t.tx * kTile + (lane & 7), py = t.ty * kTile + (lane >> 3);
     if (px < a.sw && py < a.sh) {
-        const int64_t q = (int64_t)py * a.sw + px;
-        uv = reinterpret_cast<const float2*>(a.uv)[q];
-        d = reinterpret_cast<const float4*>(a.duv)[q];
+        const int64_t i = (int64_t)py * a.sw + px;
+        uv = reinterpret_cast<const float2*>(a.uv)[i];
+        d = reinterpret_cast<const float4*>(a.duv)[i];
     }
 }
 
 // The same with a scalar tile base plus the lane's offset (the batched
 // kernel).
-__device__ __forceinline__ void load_tile_px_s(const FilterArgs& a, const StripWalk& t, int64_t band_e, float2& uv,
+__device__ __forceinline__ void load_tile_px_s(const FilterArgs& a, const TileQueue& q, TilePos t, float2& uv,
                                                float4& d)
 {
     uv = make_float2(__builtin_nanf(""), 0.f);
     d = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (t.tile >= band_e) return;
+    if (!q.has(t)) return;
     if (lane_on_screen(a, t.tx, t.ty)) {
         const int64_t p0 = tile_pixel0(a, t.tx, t.ty);
         const uint32_t lp = lane_pixel(a);
@@ -623,51 +544,58 @@ __device__ __forceinline__ void settle(const float2& uv, const float4& d)
     asm volatile("" ::"v"(uv.x), "v"(uv.y), "v"(d.x), "v"(d.y), "v"(d.z), "v"(d.w));
 }
 
-// Waves per SIMD the register budget of the single-layer kernel is sized
-// for: the collaborative methods and the 4x4 full filter need the bound of
-// three to fit in 168 registers; the others fit three anyway and keep the
-// compiler's schedule.
-template <int METHOD, int FILTER>
-constexpr int dec_waves_per_simd()
+// Dynamic LDS of a workgroup: the queues, then one slice per wave.
+constexpr int kQueueBytes = 64;
+extern __shared__ __align__(16) char dec_lds[];
+
+template <class Slice>
+__device__ __forceinline__ Slice& wave_slice()
 {
-    return METHOD == CTF_LIST || METHOD == CTF_BOX || METHOD == CTF_MASK ||
-                   (METHOD == CTF_BILINEAR4 && FILTER != CTF_FILTER_BILINEAR)
-               ? 3
-               : 2;
+    return reinterpret_cast<Slice*>(dec_lds + kQueueBytes)[wave_in_block()];
+}
+
+// Walk of the per-tile kernels: foot(uv, d) is the lanes' footprint in the
+// layer's coordinates.
+template <int METHOD, int P, bool STATS, bool FB, int FILTER, class Foot>
+__device__ __forceinline__ void tile_walk(const FilterArgs& a, DecLds& L, const InferGrid& G, const FwdWeights<P>& W,
+                                          const Biases& Bz, const TileQueue& q, FrameCounters& fc, Foot&& foot)
+{
+    // the inputs of the wave's next tile are loaded one tile ahead, its index
+    // is drawn two ahead
+    float2 uv;
+    float4 d;
+    TilePos next = q.place(wave_in_block());
+    int ahead = q.draw();
+    load_tile_px(a, q, next, uv, d);
+    settle(uv, d);
+    while (q.has(next)) {
+        const TilePos cur = next;
+        const Footprint f = foot(uv, d);
+        dec_tile<METHOD, P, STATS, FB, FILTER>(a, G, W, Bz, L, (int64_t)cur.ty * a.tiles_x + cur.tx, cur.tx, cur.ty, f,
+                                               fc, [&] {
+            next = q.place(ahead);
+            ahead = q.draw();
+            load_tile_px(a, q, next, uv, d);
+        });
+    }
 }
 
 template <int METHOD, int P, bool STATS, bool FB, int FILTER>
-__global__ __launch_bounds__(64 * kDecWaves, (dec_waves_per_simd<METHOD, FILTER>())) void k_filter_dec(
-    FilterArgs a, DevDecoderWeights D)
+__global__ __launch_bounds__(64 * kDecWavesMax) void k_filter_dec(FilterArgs a, DevDecoderWeights D)
 {
-    __shared__ DecLds lds_all[kDecWaves];
-    const int wid = wave_in_block();
     const int lane = lane_id();
-    DecLds& L = lds_all[wid];
+    int* const queues = reinterpret_cast<int*>(dec_lds);
+    queue_init(queues, 1);
     FwdWeights<P> W;
     W.load(D.w, lane);
     Biases Bz;
     Bz.load(D.bias, lane);
     const float tex_w = (float)D.grid.tex_w;
-    const Band band(a.ntiles, wid);
     FrameCounters fc;
-
-    // the inputs of the wave's next tile are loaded one tile ahead
-    float2 uv_next;
-    float4 d_next;
-    StripWalk next(band, a.ntiles, a.tiles_x);
-    load_tile_px(a, next, band.end, uv_next, d_next);
-    settle(uv_next, d_next);
-    while (next.tile < band.end) {
-        const StripWalk cur = next;
-        const float2 uv = uv_next;
-        const float4 d = d_next;
-        const Footprint f = footprint(uv.x, uv.y, d, tex_w, tex_w);
-        dec_tile<METHOD, P, STATS, FB, FILTER>(a, D.grid, W, Bz, L, cur.tile, cur.tx, cur.ty, f, fc, [&] {
-            next.advance();
-            load_tile_px(a, next, band.end, uv_next, d_next);
-        });
-    }
+    tile_walk<METHOD, P, STATS, FB, FILTER>(a, wave_slice<DecLds>(), D.grid, W, Bz, TileQueue(queues, a), fc,
+                                            [&](float2 uv, float4 d) {
+        return footprint(uv.x, uv.y, d, tex_w, tex_w);
+    });
     if (lane == 0 && a.frame_stats) fc.flush(a.frame_stats);
 }
 
@@ -688,14 +616,12 @@ constexpr bool batched()
     return !FB && METHOD != CTF_BILINEAR4;
 }
 
-// Per wave.  vals (and for the bicubic List past 16x16 rows and more, on an
-// empty batch) also serves as the sort buffer: no value is live while a tile
-// is planned.
+// Per wave.  vals also holds the sort of a List past 16x16: no value is live
+// while a tile is planned.
 template <int F>
 struct BatchLds {
     float4 vals[kMaxItems];               // decoded texels, by row
     int2 rows[kMaxItems];                 // texel coordinates to decode
-    uint64_t more[F == 4 ? kMaxItems : 1];
     uint32_t window[kWindowWords];        // window_set
     uint8_t rank[256];                    // position of the window -> item
     float2 st[kBatchSlots][kWave];        // footprint position of the lane
@@ -703,16 +629,15 @@ struct BatchLds {
     uint32_t draw[F == 4 ? kBatchSlots : 1][F == 4 ? kWave : 1];   // F = 4: draw row and flags
     int4 info[kBatchSlots];               // tile x, y, first row, whether wholly on screen
 };
-static_assert(offsetof(BatchLds<4>, rows) == 16 * kMaxItems && offsetof(BatchLds<4>, more) == 24 * kMaxItems,
-              "sort buffer layout");
+static_assert(sizeof(SegmentScratch<4>) <= kMaxItems * sizeof(float4), "sort in vals");
 
 // Per-lane flags over the draw row.
 constexpr uint32_t kExact = 1u << 15, kDraws = 1u << 14;
 
 // Plan one tile on the batch's rows from `base`: decisions, rows, per-lane
 // state of `slot`, debug outputs, tile record and counters.  Returns the
-// tile's row count, or -1, with nothing written, if the tile needs an empty
-// batch (its rows do not fit behind the others, or it sorts).
+// tile's row count, or -1, with nothing written, if its rows do not fit behind
+// the others.
 template <int METHOD, bool STATS, int FILTER>
 __device__ __forceinline__ int plan_tile(const FilterArgs& a, BatchLds<Taps<FILTER>::F>& BL, int slot, int base,
                                          int64_t tile, int tx, int ty, const WaveFootprint& f, FrameCounters& fc)
@@ -720,7 +645,7 @@ __device__ __forceinline__ int plan_tile(const FilterArgs& a, BatchLds<Taps<FILT
     constexpr int F = Taps<FILTER>::F, O = Taps<FILTER>::O;
     constexpr bool kCollab = collaborative(METHOD);
     constexpr bool kWindowed = METHOD == CTF_LIST || METHOD == CTF_MASK;
-    uint64_t* const keys = reinterpret_cast<uint64_t*>(BL.vals);
+    auto& seg = reinterpret_cast<SegmentScratch<F>&>(BL.vals);
     const int lane = lane_id();
     const bool inside = tile_interior(a, tx, ty);
     const uint64_t act = f.act, A = f.A;
@@ -750,9 +675,6 @@ __device__ __forceinline__ int plan_tile(const FilterArgs& a, BatchLds<Taps<FILT
         bbh = wave_max(inA ? oy + F - 1 : INT32_MIN) - ymin + 1;
     }
     const bool fits16 = window || (A && bbw <= 16 && bbh <= 16);
-    if constexpr (F == 4 && (METHOD == CTF_LIST || STATS)) {
-        if (A && !fits16 && base > 0) return -1;   // the sort buffer covers the rows
-    }
 
     const int corner = lane_in(A) ? 16 * (oy - ymin) + (ox - xmin) : 0;
     WindowSet S{0u, 0u, 0};
@@ -769,7 +691,7 @@ __device__ __forceinline__ int plan_tile(const FilterArgs& a, BatchLds<Taps<FILT
     }
 
     const int k = a.max_evals;
-    int n = 0;
+    int n = 0, n0 = 0;
     bool cap_ok = true, count_ok = true, success = false, sorted = false;
     int unique = S.n;
     if constexpr (METHOD == CTF_BOX) {
@@ -786,7 +708,7 @@ __device__ __forceinline__ int plan_tile(const FilterArgs& a, BatchLds<Taps<FILT
     } else if constexpr (METHOD == CTF_LIST) {
         n = S.n;
         if (A && !fits16) {
-            n = dec_list_sorted<F>(keys, lane_in(A), ox, oy, xmin, ymin);
+            n = segment_sort(seg, BL.rank, lane_in(A), 0, ox, oy, xmin, ymin, n0);
             sorted = true;
         }
         unique = n;
@@ -794,7 +716,7 @@ __device__ __forceinline__ int plan_tile(const FilterArgs& a, BatchLds<Taps<FILT
         success = nA > 0 && count_ok;
     }
     if constexpr (STATS && METHOD != CTF_LIST) {
-        if (A && !fits16) unique = dec_list_sorted<F>(keys, lane_in(A), ox, oy, xmin, ymin);
+        if (A && !fits16) unique = segment_sort(seg, BL.rank, lane_in(A), 0, ox, oy, xmin, ymin, n0);
     }
     if (nA == 0) unique = 0;
 
@@ -829,26 +751,21 @@ __device__ __forceinline__ int plan_tile(const FilterArgs& a, BatchLds<Taps<FILT
         if (STATS && a.lists) reinterpret_cast<int2*>(a.lists)[(size_t)tile * kMaxItems + i] = c;
     };
     if (success) {
-        if (METHOD == CTF_BOX || sorted) {
+        if (METHOD == CTF_BOX) {
             for (int i = lane; i < ns; i += kWave) {
-                int2 c;
-                if (METHOD == CTF_BOX) {
-                    c = make_int2(xmin + i % bbw, ymin + i / bbw);
-                } else {
-                    const uint64_t key = keys[i];
-                    c = make_int2(xmin + (int)(uint32_t)key, ymin + (int)(key >> 32));
-                }
+                const int2 c = make_int2(xmin + i % bbw, ymin + i / bbw);
                 dst[i] = c;
                 list_out(i, c);
             }
-            if (METHOD == CTF_BOX) {
 #pragma unroll
-                for (int r = 0; r < F; ++r) item[r] = (ox - xmin) + (oy + r - ymin) * bbw;
-            } else if (lane_in(A)) {
+            for (int r = 0; r < F; ++r) item[r] = (ox - xmin) + (oy + r - ymin) * bbw;
+        } else if (sorted) {
+            segment_emit(seg, [&](int i, int, int dx, int dy) {
+                dst[i] = make_int2(xmin + dx, ymin + dy);
+                list_out(i, make_int2(xmin + dx, ymin + dy));
+            });
 #pragma unroll
-                for (int r = 0; r < F; ++r)
-                    item[r] = dec_list_find(keys, n, ((uint64_t)(uint32_t)(oy + r - ymin) << 32) | (uint32_t)(ox - xmin));
-            }
+            for (int r = 0; r < F; ++r) item[r] = BL.rank[F * lane + r];
         } else {
             reinterpret_cast<uint32_t*>(BL.rank)[lane] = S.ranks;
             const int cx = xmin + 4 * (lane & 3), cy = ymin + (lane >> 2);
@@ -923,26 +840,25 @@ __device__ __forceinline__ void gather_tile(const FilterArgs& a, const BatchLds<
 // batches.  foot(uv, d) is the lanes' footprint in the layer's coordinates.
 template <int METHOD, int P, bool STATS, int FILTER, class Foot>
 __device__ __forceinline__ void batch_walk(const FilterArgs& a, BatchLds<Taps<FILTER>::F>& BL, const InferGrid& G,
-                                           const FwdWeights<P>& W, const Biases& Bz, const Band& band,
+                                           const FwdWeights<P>& W, const Biases& Bz, const TileQueue& q,
                                            FrameCounters& fc, Foot&& foot)
 {
-    // (the tile record's sorts run on an empty batch)
-    constexpr int kSlots = STATS ? 1 : kBatchSlots;
     int npend = 0, rows = 0, last = 0;
     bool redo = false;
-    StripWalk next(band, a.ntiles, a.tiles_x);
+    TilePos next = q.place(wave_in_block()), held{0, 0};
+    int ahead = q.draw();
     float2 uv_next;
     float4 d_next;
-    load_tile_px_s(a, next, band.end, uv_next, d_next);
+    load_tile_px_s(a, q, next, uv_next, d_next);
     for (;;) {
         // The next tile's inputs were requested before the last tile was
         // planned: wait for them here, before the gather's stores, which
         // complete in order with them.
         settle(uv_next, d_next);
-        const bool more = next.tile < band.end;
+        const bool more = q.has(next);
         // a batch is full when no slot is left or a tile like the last one
         // would not fit (plan_tile has the final word)
-        if (npend && (!more || redo || npend == kSlots || rows + last > kMaxItems)) {
+        if (npend && (!more || redo || npend == kBatchSlots || rows + last > kMaxItems)) {
             wave_lds_sync();
             decode_rows<P>(BL.rows, BL.vals, rows, G, W, Bz);
             wave_lds_sync();
@@ -958,15 +874,22 @@ __device__ __forceinline__ void batch_walk(const FilterArgs& a, BatchLds<Taps<FI
         // (copies made here: otherwise the next request goes to other
         // registers and is waited for at once, to be moved into these)
         asm volatile("" : "+v"(uv.x), "+v"(uv.y), "+v"(d.x), "+v"(d.y), "+v"(d.z), "+v"(d.w));
-        const StripWalk cur = next;
-        next.advance();
-        load_tile_px_s(a, next, band.end, uv_next, d_next);
+        const TilePos cur = next;
+        if (redo) {
+            next = held;
+        } else {
+            next = q.place(ahead);
+            ahead = q.draw();
+        }
+        load_tile_px_s(a, q, next, uv_next, d_next);
         const WaveFootprint f = foot(uv, d);
-        const int R = plan_tile<METHOD, STATS, FILTER>(a, BL, npend, rows, cur.tile, cur.tx, cur.ty, f, fc);
+        const int R = plan_tile<METHOD, STATS, FILTER>(a, BL, npend, rows, (int64_t)cur.ty * a.tiles_x + cur.tx, cur.tx,
+                                                       cur.ty, f, fc);
         redo = R < 0;
         if (redo) {
+            held = next;
             next = cur;
-            load_tile_px_s(a, next, band.end, uv_next, d_next);
+            load_tile_px_s(a, q, next, uv_next, d_next);
         } else {
             ++npend;
             rows += R;
@@ -983,22 +906,20 @@ __device__ __forceinline__ void batch_init(BatchLds<F>& BL)
 }
 
 template <int METHOD, int P, bool STATS, int FILTER>
-__global__ __launch_bounds__(64 * kDecWaves, 3) void k_filter_dec_batch(FilterArgs a, DevDecoderWeights D)
+__global__ __launch_bounds__(64 * kDecWavesMax) void k_filter_dec_batch(FilterArgs a, DevDecoderWeights D)
 {
-    constexpr int F = Taps<FILTER>::F;
-    __shared__ BatchLds<F> lds_all[kDecWaves];
-    const int wid = wave_in_block();
     const int lane = lane_id();
-    BatchLds<F>& BL = lds_all[wid];
+    auto& BL = wave_slice<BatchLds<Taps<FILTER>::F>>();
+    int* const queues = reinterpret_cast<int*>(dec_lds);
     batch_init(BL);
+    queue_init(queues, 1);
     FwdWeights<P> W;
     W.load(D.w, lane);
     Biases Bz;
     Bz.load(D.bias, lane);
     const float tex_w = (float)D.grid.tex_w;
-    const Band band(a.ntiles, wid);
     FrameCounters fc;
-    batch_walk<METHOD, P, STATS, FILTER>(a, BL, D.grid, W, Bz, band, fc, [&](float2 uv, float4 d) {
+    batch_walk<METHOD, P, STATS, FILTER>(a, BL, D.grid, W, Bz, TileQueue(queues, a), fc, [&](float2 uv, float4 d) {
         return wave_footprint(uv.x, uv.y, d, tex_w, tex_w);
     });
     if (lane == 0 && a.frame_stats) fc.flush(a.frame_stats);
@@ -1011,19 +932,37 @@ inline int device_cus()
     return cus > 0 ? cus : 256;
 }
 
-// Persistent grid: as many workgroups as fit on the device at once (from the
-// kernel's register and LDS use), a multiple of the 8 XCDs.
-template <typename K>
-int64_t resident_blocks(K kernel, int threads, int64_t work_blocks, int64_t min_blocks)
+// Persistent grid: the workgroups that fill the chip with three waves per
+// SIMD, a multiple of the 8 XCDs.  Twelve waves per workgroup once every wave
+// has two tiles (see TileQueue); below, four, so that a small frame spreads
+// over all CUs.
+struct DecLaunch {
+    int threads;
+    int64_t blocks;
+    unsigned lds;
+};
+
+template <class Slice>
+DecLaunch dec_launch(const FilterArgs& a, int layers)
 {
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, 0) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    int64_t blocks = (int64_t)device_cus() * per_cu;
-    if (blocks < min_blocks) blocks = min_blocks;
-    if (blocks > work_blocks) blocks = work_blocks;
-    return (blocks + 7) / 8 * 8;
+    static_assert(kQueueBytes + kDecWavesMax * sizeof(Slice) <= 160 * 1024, "a workgroup's LDS");
+    const int64_t cus = device_cus();
+    const int waves = a.ntiles >= 2 * cus * kDecWavesMax ? kDecWavesMax : kDecWavesMin;
+    DecLaunch g;
+    g.threads = 64 * waves;
+    g.blocks = (a.ntiles + waves - 1) / waves;
+    if (g.blocks > cus * (kDecWavesMax / waves)) g.blocks = cus * (kDecWavesMax / waves);
+    // one wave may take its workgroup's whole share (32-bit frame counters):
+    // at most the frame's tiles and a strip per XCD, shared by the workgroups
+    const int64_t least = counter_min_blocks((a.ntiles + (int64_t)8 * kStripRows * a.tiles_x) * layers, 1);
+    if (g.blocks < least) g.blocks = least;
+    g.blocks = (g.blocks + 7) / 8 * 8;
+    g.lds = (unsigned)(kQueueBytes + waves * sizeof(Slice));
+    return g;
 }
+
+// Tile indices of an XCD are 32-bit (2^30 tiles are 1 TB of output).
+inline bool dec_indexable(const FilterArgs& a) { return a.ntiles <= (int64_t)1 << 30; }
 
 // Instantiation for the call's statistics and fallback flags; waves of a
 // collaborative method carry the C / C+ code only when it is asked for, so
@@ -1047,16 +986,15 @@ struct GoFilter {
     struct Go {
         static hipError_t run(const FilterArgs& a, const DevDecoderWeights& d, hipStream_t s)
         {
-            const int64_t work = (a.ntiles + kDecWaves - 1) / kDecWaves;
-            const int64_t least = dec_min_blocks(a.ntiles, a.tiles_x, 1);
+            if (!dec_indexable(a)) return hipErrorInvalidValue;
             if constexpr (batched<METHOD, FB>()) {
-                auto k = k_filter_dec_batch<METHOD, P, STATS, FILTER>;
-                const int64_t blocks = resident_blocks(k, 64 * kDecWaves, work, least);
-                hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(64 * kDecWaves), 0, s, a, d);
+                const DecLaunch g = dec_launch<BatchLds<Taps<FILTER>::F>>(a, 1);
+                hipLaunchKernelGGL((k_filter_dec_batch<METHOD, P, STATS, FILTER>), dim3((unsigned)g.blocks),
+                                   dim3((unsigned)g.threads), g.lds, s, a, d);
             } else {
-                auto k = k_filter_dec<METHOD, P, STATS, FB, FILTER>;
-                const int64_t blocks = resident_blocks(k, 64 * kDecWaves, work, least);
-                hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(64 * kDecWaves), 0, s, a, d);
+                const DecLaunch g = dec_launch<DecLds>(a, 1);
+                hipLaunchKernelGGL((k_filter_dec<METHOD, P, STATS, FB, FILTER>), dim3((unsigned)g.blocks),
+                                   dim3((unsigned)g.threads), g.lds, s, a, d);
             }
             return hipGetLastError();
         }
@@ -1081,6 +1019,7 @@ hipError_t launch_dec_p(const FilterArgs& a, const DevDecoderWeights& d, hipStre
 // layer's latent grids stay resident in the L2 while its tiles are walked;
 // each wave reloads the MLP weights once per layer.
 constexpr int kMaxLayers = 8;
+static_assert(kMaxLayers * sizeof(int) <= kQueueBytes, "a queue per layer");
 
 struct LayerSet {
     DevDecoderWeights dec[kMaxLayers];
@@ -1099,16 +1038,13 @@ struct LayerLds<METHOD, false, FILTER> {
 };
 
 template <int METHOD, int P, bool STATS, bool FB, int FILTER>
-__global__ __launch_bounds__(64 * kDecWaves, (dec_waves_per_simd<METHOD, FILTER>())) void
-k_filter_layers(FilterArgs a, LayerSet LS)
+__global__ __launch_bounds__(64 * kDecWavesMax) void k_filter_layers(FilterArgs a, LayerSet LS)
 {
-    using Lds = typename LayerLds<METHOD, FB, FILTER>::Type;
-    __shared__ Lds lds_all[kDecWaves];
-    const int wid = wave_in_block();
     const int lane = lane_id();
-    Lds& L = lds_all[wid];
+    auto& L = wave_slice<typename LayerLds<METHOD, FB, FILTER>::Type>();
+    int* const queues = reinterpret_cast<int*>(dec_lds);
     if constexpr (batched<METHOD, FB>()) batch_init(L);
-    const Band band(a.ntiles, wid);
+    queue_init(queues, LS.n);
     const int64_t npix = (int64_t)a.sw * a.sh;
     FrameCounters fc;
     for (int l = 0; l < LS.n; ++l) {
@@ -1137,26 +1073,17 @@ k_filter_layers(FilterArgs a, LayerSet LS)
             return make_float4(__builtin_fmaf(m01, d.y, m00 * d.x), __builtin_fmaf(m11, d.y, m10 * d.x),
                                __builtin_fmaf(m01, d.w, m00 * d.z), __builtin_fmaf(m11, d.w, m10 * d.z));
         };
+        const TileQueue q(queues + l, a);
         if constexpr (batched<METHOD, FB>()) {
-            batch_walk<METHOD, P, STATS, FILTER>(al, L, D.grid, W, Bz, band, fc, [&](float2 uv, float4 d) {
+            batch_walk<METHOD, P, STATS, FILTER>(al, L, D.grid, W, Bz, q, fc, [&](float2 uv, float4 d) {
                 const float2 lu = layer_uv(uv);
                 return wave_footprint(lu.x, lu.y, layer_d(d), tex_w, tex_w);
             });
         } else {
-            float2 uv_next;
-            float4 d_next;
-            StripWalk next(band, a.ntiles, a.tiles_x);
-            load_tile_px(a, next, band.end, uv_next, d_next);
-            settle(uv_next, d_next);
-            while (next.tile < band.end) {
-                const StripWalk cur = next;
-                const float2 lu = layer_uv(uv_next);
-                const Footprint f = footprint(lu.x, lu.y, layer_d(d_next), tex_w, tex_w);
-                dec_tile<METHOD, P, STATS, FB, FILTER>(al, D.grid, W, Bz, L, cur.tile, cur.tx, cur.ty, f, fc, [&] {
-                    next.advance();
-                    load_tile_px(a, next, band.end, uv_next, d_next);
-                });
-            }
+            tile_walk<METHOD, P, STATS, FB, FILTER>(al, L, D.grid, W, Bz, q, fc, [&](float2 uv, float4 d) {
+                const float2 lu = layer_uv(uv);
+                return footprint(lu.x, lu.y, layer_d(d), tex_w, tex_w);
+            });
         }
     }
     if (lane == 0 && a.frame_stats) fc.flush(a.frame_stats);
@@ -1169,11 +1096,10 @@ struct GoLayers {
     struct Go {
         static hipError_t run(const FilterArgs& a, const LayerSet& LS, hipStream_t s)
         {
-            const int64_t work = (a.ntiles + kDecWaves - 1) / kDecWaves;
-            auto k = k_filter_layers<METHOD, P, STATS, FB, FILTER>;
-            const int64_t blocks =
-                resident_blocks(k, 64 * kDecWaves, work, dec_min_blocks(a.ntiles, a.tiles_x, LS.n));
-            hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(64 * kDecWaves), 0, s, a, LS);
+            if (!dec_indexable(a)) return hipErrorInvalidValue;
+            const DecLaunch g = dec_launch<typename LayerLds<METHOD, FB, FILTER>::Type>(a, LS.n);
+            hipLaunchKernelGGL((k_filter_layers<METHOD, P, STATS, FB, FILTER>), dim3((unsigned)g.blocks),
+                               dim3((unsigned)g.threads), g.lds, s, a, LS);
             return hipGetLastError();
         }
     };

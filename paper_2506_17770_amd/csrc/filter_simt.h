@@ -27,79 +27,16 @@ constexpr int kWavesPerBlock = 4;
 
 template <int F>
 struct WaveLds {
-    float4 vals[kMaxItems];         // produced texel values, by item index
-    uint64_t keys[kWave * F * F];   // List: sorted unique texel keys (dy << 32 | dx)
+    float4 vals[kMaxItems];         // produced texel values, by item index; the List's sort before any
+    uint64_t keys[kMaxItems];       // List past 16x16: texel of each item (int2); fallback planning
     uint16_t items[kMaxItems];      // Mask: item i -> mask position t = h(i, B)
-    uint8_t rank[256];              // Mask: position t -> item index h^-1(t, B)
+    uint8_t rank[256];              // Mask: position t -> item index h^-1(t, B); List past 16x16: first items of a
+                                    // lane's footprint rows
     uint8_t bytes[256];             // Mask: footprint-corner scatter before the ballots
 };
+static_assert(sizeof(SegmentScratch<4>) <= kMaxItems * sizeof(float4), "sort in vals");
 static_assert(kWavesPerBlock * sizeof(WaveLds<2>) + kLdsTermEntries * sizeof(int4) <= 32768,
               "a bilinear per-lane workgroup must fit five to a CU");
-
-// Exact set of the wave's texels as sorted unique keys (any box size): a
-// bitonic sort of the F^2 |A| footprint keys in LDS, then compaction of the
-// first key of every run.  Returns n = |U|; keys[0..n) hold U in (y, x)
-// order.
-template <int F>
-__device__ int list_unique_sorted(WaveLds<F>& L, bool inA, int ox, int oy, int xmin, int ymin)
-{
-    constexpr int N = kWave * F * F;
-    const int lane = lane_id();
-#pragma unroll
-    for (int q = 0; q < F * F; ++q) {
-        uint64_t key = ~0ull;
-        if (inA) {
-            const uint32_t dx = (uint32_t)(ox + q % F - xmin);
-            const uint32_t dy = (uint32_t)(oy + q / F - ymin);
-            key = ((uint64_t)dy << 32) | dx;
-        }
-        L.keys[F * F * lane + q] = key;
-    }
-    for (int size = 2; size <= N; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            wave_lds_sync();
-#pragma unroll
-            for (int h = 0; h < N / (2 * kWave); ++h) {
-                const int p = lane + kWave * h;                 // pair index
-                const int i = (p / stride) * stride * 2 + (p % stride);
-                const int j = i + stride;
-                const bool up = (i & size) == 0;
-                const uint64_t a = L.keys[i], b = L.keys[j];
-                if ((a > b) == up) {
-                    L.keys[i] = b;
-                    L.keys[j] = a;
-                }
-            }
-        }
-    }
-    // compaction in rounds of 64 keys: a write index never passes the read
-    // index, and round r writes below every key of the later rounds
-    int base = 0;
-    for (int c = 0; c < F * F; ++c) {
-        wave_lds_sync();
-        const int i = kWave * c + lane;
-        const uint64_t k = L.keys[i];
-        const bool first = k != ~0ull && (i == 0 || L.keys[i - 1] != k);
-        const uint64_t b = ballot(first);
-        wave_lds_sync();
-        if (first) L.keys[base + mbcnt(b)] = k;
-        base += popc64(b);
-    }
-    wave_lds_sync();
-    return base;
-}
-
-template <int F>
-__device__ __forceinline__ int list_find(const WaveLds<F>& L, int n, uint64_t key)
-{
-    int lo = 0, hi = n;  // first index with keys[idx] >= key
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (L.keys[mid] < key) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
-}
 
 // FB: the instantiation that plans fallback C / C+ for failed waves (the
 // others fall back to one-tap STF only and carry none of that code, which
@@ -247,7 +184,8 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (simt_min_waves<FILTER>()))
 
         // ---- step 3: the method's decision
         const int k = a.max_evals;
-        int n = 0;
+        auto& seg = reinterpret_cast<SegmentScratch<F>&>(L.vals);
+        int n = 0, n0 = 0;
         bool cap_ok = true, count_ok = true, success = false, sorted = false;
         int unique = nmask;
         if constexpr (METHOD == CTF_BOX) {
@@ -264,7 +202,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (simt_min_waves<FILTER>()))
             success = fits16 && count_ok;
         } else if constexpr (METHOD == CTF_LIST) {
             if (nA > 0 && !fits16) {
-                n = list_unique_sorted<F>(L, inA, ox, oy, xmin, ymin);
+                n = segment_sort(seg, L.rank, inA, 0, ox, oy, xmin, ymin, n0);
                 sorted = true;
             } else {
                 n = nmask;
@@ -274,7 +212,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (simt_min_waves<FILTER>()))
             success = nA > 0 && count_ok;
         }
         if constexpr (STATS && METHOD != CTF_LIST) {
-            if (nA > 0 && !fits16) unique = list_unique_sorted<F>(L, inA, ox, oy, xmin, ymin);
+            if (nA > 0 && !fits16) unique = segment_sort(seg, L.rank, inA, 0, ox, oy, xmin, ymin, n0);
         }
         if (nA == 0) unique = 0;
 
@@ -338,15 +276,18 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (simt_min_waves<FILTER>()))
             wave_lds_sync();
             if (inA) res = fallback_color<FILTER>(L, P, f, pick, xmin, ymin);
         } else {
+            if (METHOD == CTF_LIST && sorted && success) {
+                segment_emit(seg, [&](int i, int, int dx, int dy) {
+                    reinterpret_cast<int2*>(L.keys)[i] = make_int2(xmin + dx, ymin + dy);
+                });
+                wave_lds_sync();
+            }
             // texel of item i of the method's order
             auto item_xy = [&](int item) -> int2 {
                 if constexpr (METHOD == CTF_BOX) {
                     return make_int2(xmin + item % bbw, ymin + item / bbw);
                 } else {
-                    if (sorted) {
-                        const uint64_t key = L.keys[item];
-                        return make_int2(xmin + (int)(uint32_t)key, ymin + (int)(key >> 32));
-                    }
+                    if (sorted) return reinterpret_cast<const int2*>(L.keys)[item];
                     const int t = L.items[item];
                     return make_int2(xmin + (t & 15), ymin + (t >> 4));
                 }
@@ -403,12 +344,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (simt_min_waves<FILTER>()))
                         if constexpr (METHOD == CTF_BOX) {
                             return (ox - xmin) + (oy + j - ymin) * bbw;
                         } else {
-                            if (sorted) {
-                                const uint64_t key = ((uint64_t)(uint32_t)(oy + j - ymin) << 32) |
-                                                     (uint32_t)(ox - xmin);
-                                return list_find<F>(L, n, key);
-                            }
-                            return L.rank[16 * (oy + j - ymin) + (ox - xmin)];
+                            return L.rank[sorted ? F * lane + j : 16 * (oy + j - ymin) + (ox - xmin)];
                         }
                     };
                     if constexpr (F == 2) {
