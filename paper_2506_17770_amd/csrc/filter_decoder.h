@@ -86,8 +86,12 @@ __device__ __forceinline__ void decode_rows(const int2* rows, float4* vals, int 
     for (; r0 + 16 < R; r0 += 32) {
         infer_combine<P>(F, K, xa, xb);
         fetch_row<P>(rows, r0 + 32 + jf, G, K, F);
-        finish_row<P>(vals, R, r0 + j, W, Bz, xa, g);
-        finish_row<P>(vals, R, r0 + 16 + j, W, Bz, xb, g);
+        const f4 ya = mlp_forward_b<P>(W, Bz, xa, nullptr, nullptr);
+        const f4 yb = mlp_forward_b<P>(W, Bz, xb, nullptr, nullptr);
+        if (g == 0) {
+            vals[r0 + j] = make_float4(ya[0], ya[1], ya[2], ya[3]);
+            if (r0 + 16 + j < R) vals[r0 + 16 + j] = make_float4(yb[0], yb[1], yb[2], yb[3]);
+        }
     }
     // With 16 rows or fewer left the last fetch is theirs.  Otherwise it is
     // never used: wait for it here, while it is nearly done, rather than
