@@ -16,38 +16,55 @@ using namespace dec;
 
 // rgba[i] = decoder(xy[i]): 32 texels per pass (two MFMA tiles), persistent
 // waves; the same per-row instruction sequence as the filter's decode.  The
+// waves of a workgroup draw passes from an LDS counter (see TileQueue); the
 // coordinates are read two passes ahead and the latents one pass ahead (an
 // index past n reads texel n - 1).
 template <int P>
-__global__ __launch_bounds__(256, 2) void k_decoder_eval(DevDecoderWeights D, const int2* __restrict__ xy,
-                                                         int64_t n, float4* __restrict__ out)
+__global__ __launch_bounds__(64 * kDecWavesMax) void k_decoder_eval(DevDecoderWeights D, const int2* __restrict__ xy,
+                                                                    int64_t n, float4* __restrict__ out)
 {
     const int lane = lane_id();
     const int j = lane & 15, g = lane >> 4;
+    int* const queue = reinterpret_cast<int*>(dec_lds);
+    queue_init(queue, 1);
     FwdWeights<P> W;
     W.load(D.w, lane);
     Biases Bz;
     Bz.load(D.bias, lane);
-    const int64_t gw = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    const int64_t step = (int64_t)gridDim.x * (blockDim.x >> 6) * 32;
     const InferLane<P> K(D.grid, g >= 2);
     const int64_t last = n - 1;
-    int64_t f = gw * 32 + (lane & 31);
-    int2 p = xy[f < last ? f : last];
+    auto draw = [&]() -> int {
+        int i = 0;
+        if (lane == 0) i = __hip_atomic_fetch_add(queue, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        return i;
+    };
+    // first row of a drawn pass, and the coordinates this lane reads for it
+    auto first_row = [&](int drawn) -> int64_t {
+        return ((int64_t)__builtin_amdgcn_readfirstlane(drawn) * gridDim.x + blockIdx.x) * 32;
+    };
+    auto coord = [&](int64_t r) -> int2 {
+        const int64_t f = r + (lane & 31);
+        return xy[f < last ? f : last];
+    };
+    int64_t r0 = first_row(wave_in_block()), r1 = first_row(draw());
+    int ahead = draw();
+    int2 p = coord(r0);
     InferFetch F;
     infer_fetch<P>(D.grid, K, p.x, p.y, F);
-    f += step;
-    p = xy[f < last ? f : last];
-    for (int64_t r0 = gw * 32; r0 < n; r0 += step) {
+    p = coord(r1);
+    while (r0 < n) {
         u16x4 xa, xb;
         infer_combine<P>(F, K, xa, xb);
         infer_fetch<P>(D.grid, K, p.x, p.y, F);
-        f += step;
-        p = xy[f < last ? f : last];
+        const int64_t r2 = first_row(ahead);
+        ahead = draw();
+        p = coord(r2);
         const f4 ya = mlp_forward_b<P>(W, Bz, xa, nullptr, nullptr);
         const f4 yb = mlp_forward_b<P>(W, Bz, xb, nullptr, nullptr);
         if (g == 0 && r0 + j < n) out[r0 + j] = make_float4(ya[0], ya[1], ya[2], ya[3]);
         if (g == 0 && r0 + 16 + j < n) out[r0 + 16 + j] = make_float4(yb[0], yb[1], yb[2], yb[3]);
+        r0 = r1;
+        r1 = r2;
     }
 }
 
@@ -88,14 +105,17 @@ hipError_t ctf_internal_decoder_eval(const ctf_texture_s* t, const int32_t* xy, 
 {
     if (n <= 0) return hipSuccess;
     const DevDecoderWeights& d = t->dec;
-    int64_t blocks = ((n + 31) / 32 + 3) / 4;
-    const int64_t cap = (int64_t)device_cus() * 2;
-    if (blocks > cap) blocks = cap;
+    // three waves per SIMD; 12-wave workgroups once every wave has two passes
+    const int64_t cus = device_cus(), passes = (n + 31) / 32;
+    const int waves = passes >= 2 * cus * kDecWavesMax ? kDecWavesMax : kDecWavesMin;
+    int64_t blocks = (passes + waves - 1) / waves;
+    if (blocks > cus * (kDecWavesMax / waves)) blocks = cus * (kDecWavesMax / waves);
+    const dim3 block(64 * waves);
     const int2* p = reinterpret_cast<const int2*>(xy);
     float4* o = reinterpret_cast<float4*>(out);
     if (t->dec.precision == CTF_BF16)
-        hipLaunchKernelGGL(k_decoder_eval<CTF_BF16>, dim3((unsigned)blocks), dim3(256), 0, s, d, p, n, o);
+        hipLaunchKernelGGL(k_decoder_eval<CTF_BF16>, dim3((unsigned)blocks), block, kQueueBytes, s, d, p, n, o);
     else
-        hipLaunchKernelGGL(k_decoder_eval<CTF_FP16>, dim3((unsigned)blocks), dim3(256), 0, s, d, p, n, o);
+        hipLaunchKernelGGL(k_decoder_eval<CTF_FP16>, dim3((unsigned)blocks), block, kQueueBytes, s, d, p, n, o);
     return hipGetLastError();
 }
