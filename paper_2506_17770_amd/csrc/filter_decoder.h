@@ -605,14 +605,21 @@ __global__ __launch_bounds__(64 * kDecWavesMax) void k_filter_dec(FilterArgs a, 
 
 // ---------------------------------------------------------------------------
 // Batched decode (every method but the full filter, no C / C+ fallback).  A
-// wave plans up to kBatchSlots tiles, each tile's rows behind the last one's
+// wave plans up to batch_slots() tiles, each tile's rows behind the last one's
 // (at most 256 rows), decodes them in one pass and gathers the tiles, so the
 // pass's start-up and its partial last MFMA tile are shared.  A planned
 // tile's per-lane state waits in LDS until its gather, so no two tiles' state
 // is live in registers.
 // ---------------------------------------------------------------------------
 
-constexpr int kBatchSlots = 4;
+// Tiles per batch, measured at 3840x2160 with 2, 3, 4: bilinear List 139.7,
+// 139.1, 137.5 us; B-spline List, whose tiles decode 70 rows on average,
+// 184.9, 195.1, 197.9 us.
+template <int F>
+constexpr int batch_slots()
+{
+    return F == 2 ? 4 : 2;
+}
 
 template <int METHOD, bool FB>
 constexpr bool batched()
@@ -628,10 +635,11 @@ struct BatchLds {
     int2 rows[kMaxItems];                 // texel coordinates to decode
     uint32_t window[kWindowWords];        // window_set
     uint8_t rank[256];                    // position of the window -> item
-    float2 st[kBatchSlots][kWave];        // footprint position of the lane
-    uint32_t item[kBatchSlots][kWave];    // F = 2: items of the two footprint rows, draw row and flags; F = 4: items
-    uint32_t draw[F == 4 ? kBatchSlots : 1][F == 4 ? kWave : 1];   // F = 4: draw row and flags
-    int4 info[kBatchSlots];               // tile x, y, first row, whether wholly on screen
+    static constexpr int kSlots = batch_slots<F>();
+    float2 st[kSlots][kWave];             // footprint position of the lane
+    uint32_t item[kSlots][kWave];         // F = 2: items of the two footprint rows, draw row and flags; F = 4: items
+    uint32_t draw[F == 4 ? kSlots : 1][F == 4 ? kWave : 1];   // F = 4: draw row and flags
+    int4 info[kSlots];                   // tile x, y, first row, whether wholly on screen
 };
 static_assert(sizeof(SegmentScratch<4>) <= kMaxItems * sizeof(float4), "sort in vals");
 
@@ -862,7 +870,7 @@ __device__ __forceinline__ void batch_walk(const FilterArgs& a, BatchLds<Taps<FI
         const bool more = q.has(next);
         // a batch is full when no slot is left or a tile like the last one
         // would not fit (plan_tile has the final word)
-        if (npend && (!more || redo || npend == kBatchSlots || rows + last > kMaxItems)) {
+        if (npend && (!more || redo || npend == BatchLds<Taps<FILTER>::F>::kSlots || rows + last > kMaxItems)) {
             wave_lds_sync();
             decode_rows<P>(BL.rows, BL.vals, rows, G, W, Bz);
             wave_lds_sync();
