@@ -71,6 +71,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (simt_min_waves<FILTER>()))
         split_ok = kCanSplit && staged && a.split == CTF_SPLIT_AUTO;
     }
     const bool lds_float = staged && T.fterms != nullptr;
+    const bool joint = joint_texels(T, lds_float);
     auto texel = [&](int x, int y) __attribute__((always_inline)) -> float4 {
         return texel_eval_staged<TEX>(T, terms_lds, lds_float, x, y);
     };
@@ -245,25 +246,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (simt_min_waves<FILTER>()))
             P = plan_fallback<FILTER>(L, a.fallback, inA, nA, rankA, f, pick, pcg_hash(h2), fits16, xmin, ymin);
 
         if constexpr (METHOD == CTF_BILINEAR4) {
-            if (exact) {
-                if constexpr (F == 2) {
-                    const float4 v0 = texel(f.x0, f.y0);
-                    const float4 v1 = texel(f.x0 + 1, f.y0);
-                    const float4 v2 = texel(f.x0, f.y0 + 1);
-                    const float4 v3 = texel(f.x0 + 1, f.y0 + 1);
-                    res = bilerp(f.s, f.t, v0, v1, v2, v3);
-                } else {
-                    float wx[4], wy[4];
-                    taps32<FILTER>(f.s, wx);
-                    taps32<FILTER>(f.t, wy);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float4 r = row4(wx, texel(ox, oy + j), texel(ox + 1, oy + j),
-                                              texel(ox + 2, oy + j), texel(ox + 3, oy + j));
-                        res = col_acc(wy[j], r, res, j == 0);
-                    }
-                }
-            }
+            if (exact) res = full_filter<FILTER, TEX>(T, terms_lds, joint, f.s, f.t, ox, oy, texel);
         } else if (fallback) {
             // lanes of A evaluate the planned texels; minifying lanes draw
             const bool pa = inA && P.produces, pd = draws && !inA;

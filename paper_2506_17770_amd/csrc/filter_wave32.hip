@@ -300,6 +300,7 @@ __global__ __launch_bounds__(kWave * kW32Waves) void k_filter_w32(FilterArgs a, 
     constexpr bool kStage = TEX == CTF_TEX_SINUSOIDS && (METHOD == CTF_BILINEAR4 || METHOD == CTF_STF1);
     bool lds_float = false;
     if constexpr (kStage) lds_float = stage_terms(T, terms_lds) && T.fterms != nullptr;
+    const bool joint = joint_texels(T, lds_float);
     auto texel = [&](int x, int y) __attribute__((always_inline)) -> float4 {
         if constexpr (kStage) return texel_eval_staged<TEX>(T, terms_lds, lds_float, x, y);
         else return texel_eval<TEX>(T, x, y);
@@ -480,25 +481,7 @@ __global__ __launch_bounds__(kWave * kW32Waves) void k_filter_w32(FilterArgs a, 
                                                   xmin, ymin, Hm, nprod0, nprod1);
         }
         if constexpr (METHOD == CTF_BILINEAR4) {
-            if (exact) {
-                if constexpr (F == 2) {
-                    const float4 v0 = texel(f.x0, f.y0);
-                    const float4 v1 = texel(f.x0 + 1, f.y0);
-                    const float4 v2 = texel(f.x0, f.y0 + 1);
-                    const float4 v3 = texel(f.x0 + 1, f.y0 + 1);
-                    res = bilerp(f.s, f.t, v0, v1, v2, v3);
-                } else {
-                    float wx[4], wy[4];
-                    taps32<FILTER>(f.s, wx);
-                    taps32<FILTER>(f.t, wy);
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const float4 r = row4(wx, texel(ox, oy + j), texel(ox + 1, oy + j),
-                                              texel(ox + 2, oy + j), texel(ox + 3, oy + j));
-                        res = col_acc(wy[j], r, res, j == 0);
-                    }
-                }
-            }
+            if (exact) res = full_filter<FILTER, TEX>(T, terms_lds, joint, f.s, f.t, ox, oy, texel);
         } else {
             for (int round = 0; round < (kCollab ? k : 1); ++round) {
                 const int item = rankA + round * nA;
