@@ -339,41 +339,77 @@ struct WindowSet {
 constexpr int kWindowPad = 16;
 constexpr int kWindowWords = kWindowPad + kWave;
 
-// Each lane of A marks its footprint's corner byte; the FxF spread of the
-// marks is then a few byte shifts of the words of rows r, r-1, .. r-F+1 (a
+// FxF spread of the corner bytes around word w (rows r, r-1, .. r-F+1): a
 // corner sits at column <= 16 - F, so the bytes shifted in from the previous
-// word of the same row never cross a row), and the ranks are one wave-wide
-// sum.  One LDS round trip and no mask in scalar registers: the earlier form
-// (four byte reads, four ballots, 256-bit scalar shifts, a rank per ballot)
-// took four serial LDS round trips and about 130 scalar instructions.
+// word of the same row never cross a row.
 template <int F>
-__device__ __forceinline__ WindowSet window_set(uint32_t* words, bool inA, int corner)
+__device__ __forceinline__ uint32_t window_spread(const uint32_t* w)
 {
-    const int lane = lane_id();
-    uint32_t* const w = words + kWindowPad + lane;
-    *w = 0u;
-    wave_lds_sync();
-    if (inA) reinterpret_cast<uint8_t*>(words + kWindowPad)[corner] = 1;
-    wave_lds_sync();
     uint32_t cur = 0u, prev = 0u;
 #pragma unroll
     for (int r = 0; r < F; ++r) {
         cur |= w[-4 * r];
         prev |= w[-4 * r - 1];
     }
-    WindowSet S;
-    S.set = cur;
+    uint32_t set = cur;
 #pragma unroll
-    for (int c = 1; c < F; ++c) S.set |= __builtin_amdgcn_alignbyte(cur, prev, 4 - c);
+    for (int c = 1; c < F; ++c) set |= __builtin_amdgcn_alignbyte(cur, prev, 4 - c);
+    return set;
+}
+
+// Ranks of a word's four positions: exclusive byte sums inside the word plus
+// the lane's base in each byte (a rank is below 256, so no byte carries).
+__device__ __forceinline__ uint32_t window_ranks(uint32_t set, uint32_t base)
+{
+    uint32_t t = (set << 8) + set;
+    t = (t << 16) + t;
+    return (t << 8) + __builtin_amdgcn_perm(0u, base, 0u);
+}
+
+// Each lane of A marks its footprint's corner byte; the distinct texels are
+// the FxF spread of the marks, and the ranks one wave-wide sum.  One LDS
+// round trip and no mask in scalar registers: the earlier form (four byte
+// reads, four ballots, 256-bit scalar shifts, a rank per ballot) took four
+// serial LDS round trips and about 130 scalar instructions.
+template <int F>
+__device__ __forceinline__ WindowSet window_set(uint32_t* words, bool inA, int corner)
+{
+    uint32_t* const w = words + kWindowPad + lane_id();
+    *w = 0u;
+    wave_lds_sync();
+    if (inA) reinterpret_cast<uint8_t*>(words + kWindowPad)[corner] = 1;
+    wave_lds_sync();
+    WindowSet S;
+    S.set = window_spread<F>(w);
     const int cnt = (int)__builtin_amdgcn_sad_u8(S.set, 0u, 0u);
     const int incl = wave_scan(cnt);
     S.n = __builtin_amdgcn_readlane(incl, 63);
-    // exclusive byte sums inside the word, plus the lane's base in each byte
-    // (a rank is below 256, so no byte carries)
-    uint32_t t = S.set + (S.set << 8);
-    t += t << 16;
-    S.ranks = (t << 8) + __builtin_amdgcn_perm(0u, (uint32_t)(incl - cnt), 0u);
+    S.ranks = window_ranks(S.set, (uint32_t)(incl - cnt));
     return S;
+}
+
+// The same for the two half-waves' windows (words: two windows of
+// kWindowWords, half 0 first): every lane holds four positions of each, and
+// both counts go through one sum.
+template <int F>
+__device__ __forceinline__ void window_set_halves(uint32_t* words, bool inA, int half, int corner, WindowSet S[2])
+{
+    uint32_t* const w0 = words + kWindowPad + lane_id();
+    uint32_t* const w1 = w0 + kWindowWords;
+    *w0 = 0u;
+    *w1 = 0u;
+    wave_lds_sync();
+    if (inA) reinterpret_cast<uint8_t*>(words + kWindowPad)[4 * kWindowWords * half + corner] = 1;
+    wave_lds_sync();
+    S[0].set = window_spread<F>(w0);
+    S[1].set = window_spread<F>(w1);
+    const int cnt = (int)(__builtin_amdgcn_sad_u8(S[0].set, 0u, 0u) | (__builtin_amdgcn_sad_u8(S[1].set, 0u, 0u) << 16));
+    const int incl = wave_scan(cnt);
+    const int n = __builtin_amdgcn_readlane(incl, 63);
+    S[0].n = n & 0xffff;
+    S[1].n = n >> 16;
+    S[0].ranks = window_ranks(S[0].set, (uint32_t)((incl - cnt) & 0xffff));
+    S[1].ranks = window_ranks(S[1].set, (uint32_t)((incl - cnt) >> 16));
 }
 
 // The distinct texels of footprints that do not fit a window (any box size).

@@ -21,16 +21,23 @@ namespace {
 constexpr int kW32Waves = 4;
 constexpr int kHalfItems = kMaxItems / 2;  // n <= k |A| <= 4 * 32 per half
 
-template <int F>
 struct W32Lds {
-    float4 vals[2][kHalfItems];   // produced texel values, by half and item
-    uint64_t keys[kWave * F * F]; // List past 16x16: sorted unique keys, half in bit 62
-    uint16_t items[2][256];       // Mask: item i -> position t = h(i, B)
+    float4 vals[2][kHalfItems];   // produced texel values, by half and item; the List's sort before any
+    // per half: the texels of a List past 16x16 by item, or (a failed half)
+    // fallback C+'s footprints, or the texels produced by C past 16x16
+    union Half {
+        int2 list[kHalfItems];
+        StashEntry stash[32];
+        int2 produced[32];
+    } half[2];
+    uint32_t window[2 * kWindowWords];   // window_set_halves; fallback C+: byte scatter
+    uint8_t items[2][256];        // Mask: item i -> position t = h(i, B)
     uint8_t rank[2][256];         // Mask: position t -> item index h^-1(t, B); fallback: slot + 1
-    uint8_t bytes[2][256];        // footprint-corner scatter before the ballots
-    StashEntry stash[2][32];      // fallback C+: each lane's footprint, by half
-    int2 produced[2][32];         // fallback C past 16x16: the produced texels, by slot
+    uint8_t first[256];           // List past 16x16: first items of each lane's footprint rows
+    __device__ uint8_t* bytes(int h) { return reinterpret_cast<uint8_t*>(window + kWindowPad + kWindowWords * h); }
 };
+static_assert(sizeof(SegmentScratch<4>) <= 2 * kHalfItems * sizeof(float4), "sort in vals");
+static_assert(kW32Waves * sizeof(W32Lds) + kLdsTermEntries * sizeof(int4) <= 40960, "four workgroups per CU");
 
 // min/max over each half-wave (all 64 lanes active): DPP over the 16-lane
 // rows, then rows 0,1 make half 0 and rows 2,3 half 1.
@@ -48,66 +55,6 @@ __device__ __forceinline__ void halves_reduce(int v, Op op, int& r0, int& r1)
 __device__ __forceinline__ uint32_t lo32(uint64_t m) { return (uint32_t)m; }
 __device__ __forceinline__ uint32_t hi32(uint64_t m) { return (uint32_t)(m >> 32); }
 
-// Sorted unique keys of both halves (half 0 first) over the FxF footprints
-// with upper-left taps (ox, oy); returns the total and the number of half-0
-// keys in n0.
-template <int F>
-__device__ int w32_list_sorted(W32Lds<F>& L, bool inA, int h, int ox, int oy, int xmin, int ymin, int& n0)
-{
-    constexpr int N = kWave * F * F;
-    const int lane = lane_id();
-#pragma unroll
-    for (int q = 0; q < F * F; ++q) {
-        uint64_t key = ~0ull;
-        if (inA)
-            key = ((uint64_t)h << 62) | ((uint64_t)(uint32_t)(oy + q / F - ymin) << 32) |
-                  (uint32_t)(ox + q % F - xmin);
-        L.keys[F * F * lane + q] = key;
-    }
-    for (int size = 2; size <= N; size <<= 1)
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            wave_lds_sync();
-#pragma unroll
-            for (int hh = 0; hh < N / (2 * kWave); ++hh) {
-                const int p = lane + kWave * hh;
-                const int i = (p / stride) * stride * 2 + (p % stride);
-                const int j = i + stride;
-                const bool up = (i & size) == 0;
-                const uint64_t x = L.keys[i], y = L.keys[j];
-                if ((x > y) == up) {
-                    L.keys[i] = y;
-                    L.keys[j] = x;
-                }
-            }
-        }
-    int base = 0;
-    n0 = 0;
-    for (int c = 0; c < N / kWave; ++c) {
-        wave_lds_sync();
-        const int i = kWave * c + lane;
-        const uint64_t k = L.keys[i];
-        const bool first = k != ~0ull && (i == 0 || L.keys[i - 1] != k);
-        const uint64_t b = ballot(first);
-        n0 += popc64(ballot(first && (k >> 62) == 0));
-        wave_lds_sync();
-        if (first) L.keys[base + mbcnt(b)] = k;
-        base += popc64(b);
-    }
-    wave_lds_sync();
-    return base;
-}
-
-template <int F>
-__device__ __forceinline__ int w32_find(const W32Lds<F>& L, int lo, int hi, uint64_t key)
-{
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (L.keys[mid] < key) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
-}
-
 // Fallbacks C and C+ (Section 3.4, Eq. 1 and Eq. 2) per half-wave: the
 // wave64 planning of fallback.h with every ballot, rank and table taken over
 // the lanes of one 8x4 tile, so Eq. 2 spreads the spare lanes of a 32-lane
@@ -120,7 +67,7 @@ struct W32Fallback {
 };
 
 template <int FILTER, int F>
-__device__ W32Fallback plan_fallback_w32(W32Lds<F>& L, int fb, bool fbl, bool inA, int h, int nA, int rankA,
+__device__ W32Fallback plan_fallback_w32(W32Lds& L, int fb, bool fbl, bool inA, int h, int nA, int rankA,
                                          const Footprint& f, int2 pick, uint32_t h3, bool fits16, int xmin, int ymin,
                                          uint64_t Hm, int& nprod0, int& nprod1)
 {
@@ -132,21 +79,20 @@ __device__ W32Fallback plan_fallback_w32(W32Lds<F>& L, int fb, bool fbl, bool in
     P.table = fits16;
     if (fb == CTF_FB_CPLUS && ballot(fbl && fits16) != 0) {
         const bool cplus = fbl && fits16;
-        reinterpret_cast<uint32_t*>(L.bytes)[lane] = 0u;
-        reinterpret_cast<uint32_t*>(L.bytes)[kWave + lane] = 0u;
-        L.stash[h][ll] = StashEntry{f.x0, f.y0, f.s, f.t};
+        reinterpret_cast<uint32_t*>(L.bytes(0))[lane] = 0u;
+        reinterpret_cast<uint32_t*>(L.bytes(1))[lane] = 0u;
+        if (cplus) L.half[h].stash[ll] = StashEntry{f.x0, f.y0, f.s, f.t};
         wave_lds_sync();
-        if (mine && cplus) L.bytes[h][16 * (pick.y - ymin) + (pick.x - xmin)] = 1;
+        if (mine && cplus) L.bytes(h)[16 * (pick.y - ymin) + (pick.x - xmin)] = 1;
         wave_lds_sync();
         // S per half: the distinct drawn texels of its lanes of A
         uint64_t S0[4], S1[4];
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-            const uint64_t b0 = ballot(L.bytes[h][64 * w + ll] != 0);
-            const uint64_t b1 = ballot(L.bytes[h][64 * w + 32 + ll] != 0);
-            S0[w] = (uint64_t)lo32(b0) | ((uint64_t)lo32(b1) << 32);
-            S1[w] = (uint64_t)hi32(b0) | ((uint64_t)hi32(b1) << 32);
+            S0[w] = ballot(L.bytes(0)[64 * w + lane] != 0);
+            S1[w] = ballot(L.bytes(1)[64 * w + lane] != 0);
         }
+        // items of the failed halves only: the other half keeps its own
         int ns0 = 0, ns1 = 0;
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
@@ -154,7 +100,7 @@ __device__ W32Fallback plan_fallback_w32(W32Lds<F>& L, int fb, bool fbl, bool in
             int base = 0;
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
-                if ((Sh[w] >> lane) & 1u) L.items[hh][base + mbcnt(Sh[w])] = (uint16_t)(64 * w + lane);
+                if ((Sh[w] >> lane) & 1u) L.items[hh][base + mbcnt(Sh[w])] = (uint8_t)(64 * w + lane);
                 base += popc64(Sh[w]);
             }
             if (hh) ns1 = base;
@@ -162,7 +108,7 @@ __device__ W32Fallback plan_fallback_w32(W32Lds<F>& L, int fb, bool fbl, bool in
         }
         wave_lds_sync();
         // lane of each rank of A in its half (the bytes are free after the ballots)
-        if (inA) L.bytes[h][rankA] = (uint8_t)ll;
+        if (inA) L.bytes(h)[rankA] = (uint8_t)ll;
         wave_lds_sync();
         if (mine && cplus) {
             const int ns = h ? ns1 : ns0;
@@ -173,7 +119,7 @@ __device__ W32Fallback plan_fallback_w32(W32Lds<F>& L, int fb, bool fbl, bool in
                 P.texel = make_int2(xmin + (t & 15), ymin + (t >> 4));
             } else {
                 constexpr int O = Taps<FILTER>::O;
-                const StashEntry T = L.stash[h][L.bytes[h][cplus_target(nA, ns, rankA)]];
+                const StashEntry T = L.half[h].stash[L.bytes(h)[cplus_target(nA, ns, rankA)]];
                 float wx[4], wy[4];
                 taps32<FILTER>(T.s, wx);
                 taps32<FILTER>(T.t, wy);
@@ -221,7 +167,7 @@ __device__ W32Fallback plan_fallback_w32(W32Lds<F>& L, int fb, bool fbl, bool in
     wave_lds_sync();
     if (P.produces) {
         if (P.table) L.rank[h][16 * (P.texel.y - ymin) + (P.texel.x - xmin)] = (uint8_t)(P.slot + 1);
-        else L.produced[h][P.slot] = P.texel;
+        else L.half[h].produced[P.slot] = P.texel;
     }
     wave_lds_sync();
     return P;
@@ -230,7 +176,7 @@ __device__ W32Fallback plan_fallback_w32(W32Lds<F>& L, int fb, bool fbl, bool in
 // Eq. 1 for a lane of A of a fallback half (fallback_color of fallback.h over
 // this half's slots).
 template <int FILTER, int F>
-__device__ float4 fallback_color_w32(const W32Lds<F>& L, const W32Fallback& P, int h, int nprod, const Footprint& f,
+__device__ float4 fallback_color_w32(const W32Lds& L, const W32Fallback& P, int h, int nprod, const Footprint& f,
                                      int2 pick, int xmin, int ymin)
 {
     constexpr int O = Taps<FILTER>::O;
@@ -249,7 +195,7 @@ __device__ float4 fallback_color_w32(const W32Lds<F>& L, const W32Fallback& P, i
             slot = (int)L.rank[h][16 * (y - ymin) + (x - xmin)] - 1;
         } else {
             for (int r = 0; r < nprod; ++r) {
-                const int2 e = L.produced[h][r];
+                const int2 e = L.half[h].produced[r];
                 if (e.x == x && e.y == y) {
                     slot = r;
                     break;
@@ -281,115 +227,142 @@ struct HalfDecision {
     bool cap_ok, count_ok, success;
 };
 
+// Five instructions per term need the terms in vector registers (from LDS by
+// broadcast: a vector instruction reads one scalar register); with the LDS
+// slices and the staged terms four workgroups fit a CU.
 template <int METHOD, int TEX, bool STATS, int FILTER, bool FB>
-__global__ __launch_bounds__(kWave * kW32Waves) void k_filter_w32(FilterArgs a, DevTexture T)
+__global__ __launch_bounds__(kWave * kW32Waves, 4) void k_filter_w32(FilterArgs a, DevTexture T)
 {
     constexpr int F = Taps<FILTER>::F, O = Taps<FILTER>::O;
-    __shared__ W32Lds<F> lds_all[kW32Waves];
-    __shared__ int4 terms_lds[TEX == CTF_TEX_SINUSOIDS && (METHOD == CTF_BILINEAR4 || METHOD == CTF_STF1)
-                                  ? kLdsTermEntries
-                                  : 1];
+    constexpr bool kStage = TEX == CTF_TEX_SINUSOIDS;
+    constexpr bool kCollab = METHOD == CTF_LIST || METHOD == CTF_BOX || METHOD == CTF_MASK;
+    constexpr bool kWindowed = METHOD == CTF_LIST || METHOD == CTF_MASK;
+    __shared__ W32Lds lds_all[kW32Waves];
+    __shared__ int4 terms_lds[kStage ? kLdsTermEntries : 1];
     const int wid = wave_in_block();
     const int lane = lane_id();
     const int h = lane >> 5, ll = lane & 31;
-    W32Lds<F>& L = lds_all[wid];
-    // Terms from LDS for the 4-tap and one-tap kernels; the collaborative
-    // ones keep them in scalar registers (the LDS copy and the extra vector
-    // registers cost them occupancy: List 8x4 at 1080p 21.3 against 24.0
-    // Gpixels/s)
-    constexpr bool kStage = TEX == CTF_TEX_SINUSOIDS && (METHOD == CTF_BILINEAR4 || METHOD == CTF_STF1);
+    W32Lds& L = lds_all[wid];
+    if (lane < kWindowPad) L.window[lane] = L.window[kWindowWords + lane] = 0u;
     bool lds_float = false;
     if constexpr (kStage) lds_float = stage_terms(T, terms_lds) && T.fterms != nullptr;
     const bool joint = joint_texels(T, lds_float);
     auto texel = [&](int x, int y) __attribute__((always_inline)) -> float4 {
-        if constexpr (kStage) return texel_eval_staged<TEX>(T, terms_lds, lds_float, x, y);
-        else return texel_eval<TEX>(T, x, y);
+        return texel_eval_staged<TEX>(T, terms_lds, lds_float, x, y);
+    };
+    auto half_mask = [](uint64_t m, int hh) -> uint64_t {
+        return hh ? m & 0xffffffff00000000ull : m & 0x00000000ffffffffull;
     };
     FrameCounters fc;
-    const int64_t npairs = (a.ntiles + 1) / 2;
+    // Pairs of tiles, the inputs of the wave's next pair loaded one pair
+    // ahead; loads and the output store are unconditional (see
+    // k_filter_simt).  A walk's tile is the pair's first, its second the next
+    // one in row-major order.
     const int64_t nw = (int64_t)gridDim.x * kW32Waves;
-    for (int64_t pair = (int64_t)blockIdx.x * kW32Waves + wid; pair < npairs; pair += nw) {
-        const int64_t tile = 2 * pair + h;
-        const bool tile_ok = tile < a.ntiles;
-        const int tx = tile_ok ? (int)(tile % a.tiles_x) : 0, ty = tile_ok ? (int)(tile / a.tiles_x) : 0;
+    auto place = [&](const TileWalk& w, int& tx, int& ty) __attribute__((always_inline)) -> bool {
+        const bool wrap = w.tx + 1 >= a.tiles_x;
+        tx = h ? (wrap ? 0 : w.tx + 1) : w.tx;
+        ty = h && wrap ? w.ty + 1 : w.ty;
+        return w.tile + h < a.ntiles;
+    };
+    auto load_px = [&](const TileWalk& w, float2& uv, float4& d) __attribute__((always_inline)) -> bool {
+        int tx, ty;
+        const bool tile_ok = place(w, tx, ty);
+        const int qx = tx * 8 + (ll & 7), qy = ty * 4 + (ll >> 3);
+        const bool ok = tile_ok && qx < a.sw && qy < a.sh;
+        const int64_t q = ok ? (int64_t)qy * a.sw + qx : 0;
+        uv = reinterpret_cast<const float2*>(a.uv)[q];
+        d = reinterpret_cast<const float4*>(a.duv)[q];
+        return ok;
+    };
+    TileWalk next(2 * ((int64_t)blockIdx.x * kW32Waves + wid), 2 * nw, a.tiles_x);
+    float2 uv_next;
+    float4 d_next;
+    bool ok_next = load_px(next, uv_next, d_next);
+    asm volatile("" ::"v"(uv_next.x), "v"(uv_next.y), "v"(d_next.x), "v"(d_next.y), "v"(d_next.z), "v"(d_next.w));
+    while (next.tile < a.ntiles) {
+        const TileWalk cur = next;
+        const float2 uv_cur = ok_next ? uv_next : make_float2(__builtin_nanf(""), 0.f);
+        const float4 d_cur = ok_next ? d_next : make_float4(0.f, 0.f, 0.f, 0.f);
+        next.advance(2 * nw);
+        ok_next = load_px(next, uv_next, d_next);
+        int tx, ty;
+        const bool tile_ok = place(cur, tx, ty);
+        const int64_t tile = cur.tile + h;
         const int px = tx * 8 + (ll & 7), py = ty * 4 + (ll >> 3);
         const bool in_screen = tile_ok && px < a.sw && py < a.sh;
         const int64_t pix = (int64_t)py * a.sw + px;
 
-        Footprint f;
-        {
-            float2 uv = make_float2(__builtin_nanf(""), 0.f);
-            float4 d = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (in_screen) {
-                uv = reinterpret_cast<const float2*>(a.uv)[pix];
-                d = reinterpret_cast<const float4*>(a.duv)[pix];
-            }
-            f = footprint(uv.x, uv.y, d, (float)T.width, (float)T.height);
-        }
-        const bool inA = f.active && f.magnify;
+        const WaveFootprint f = wave_footprint(uv_cur.x, uv_cur.y, d_cur, (float)T.width, (float)T.height);
+        const bool inA = lane_in(f.A);
         const int ox = f.x0 - O, oy = f.y0 - O;   // upper-left tap of the FxF footprint
-        const uint64_t act = ballot(f.active);
-        const uint64_t Aw = ballot(inA);
-        const uint64_t Hm = h ? 0xffffffff00000000ull : 0x00000000ffffffffull;
-        const uint64_t A = Aw & Hm;
-        const int nA0 = __popc(lo32(Aw)), nA1 = __popc(hi32(Aw));
-        const int nA = h ? nA1 : nA0;
-        const int rankA = mbcnt(A);
+        // (an opaque second half: as "A < 2^32" the test for an empty one became
+        // a vector compare, and this compiler then lost the scalar condition
+        // between two selects on it)
+        uint32_t A0 = lo32(f.A), A1 = hi32(f.A);
+        asm("" : "+s"(A0), "+s"(A1));
+        const int nAs[2] = {(int)__popc(A0), (int)__popc(A1)};
+        const int nA = h ? nAs[1] : nAs[0];
+        const int rankA = h ? mbcnt(half_mask(f.A, 1)) : mbcnt(half_mask(f.A, 0));
 
-        // ---- box per half
-        int xmin0 = 0, ymin0 = 0, xmax0 = -1, ymax0 = -1, xmin1 = 0, ymin1 = 0, xmax1 = -1, ymax1 = -1;
-        constexpr bool kCollab = METHOD == CTF_LIST || METHOD == CTF_BOX || METHOD == CTF_MASK;
-        if ((kCollab || STATS) && (nA0 | nA1)) {
-            halves_reduce(inA ? ox : INT32_MAX, MinOp(), xmin0, xmin1);
-            halves_reduce(inA ? oy : INT32_MAX, MinOp(), ymin0, ymin1);
-            halves_reduce(inA ? ox + F - 1 : INT32_MIN, MaxOp(), xmax0, xmax1);
-            halves_reduce(inA ? oy + F - 1 : INT32_MIN, MaxOp(), ymax0, ymax1);
-        }
-        const int bbw0 = nA0 ? xmax0 - xmin0 + 1 : 0, bbh0 = nA0 ? ymax0 - ymin0 + 1 : 0;
-        const int bbw1 = nA1 ? xmax1 - xmin1 + 1 : 0, bbh1 = nA1 ? ymax1 - ymin1 + 1 : 0;
-        if (!nA0) xmin0 = ymin0 = 0;
-        if (!nA1) xmin1 = ymin1 = 0;
-        const bool fits0 = nA0 > 0 && bbw0 <= 16 && bbh0 <= 16;
-        const bool fits1 = nA1 > 0 && bbw1 <= 16 && bbh1 <= 16;
-        const int xmin = h ? xmin1 : xmin0, ymin = h ? ymin1 : ymin0;
-        const int bbw = h ? bbw1 : bbw0;
-        const bool fits16 = h ? fits1 : fits0;
-
-        // ---- 16x16 masks per half: corner bytes, 8 ballots, corner spread
-        uint64_t B0[4] = {0, 0, 0, 0}, B1[4] = {0, 0, 0, 0};
-        int nmask0 = 0, nmask1 = 0;
-        constexpr bool kNeedMask = METHOD == CTF_MASK || METHOD == CTF_LIST || STATS;
-        if (kNeedMask && (fits0 || fits1)) {
-            reinterpret_cast<uint32_t*>(L.bytes)[lane] = 0u;
-            reinterpret_cast<uint32_t*>(L.bytes)[kWave + lane] = 0u;
-            wave_lds_sync();
-            if (inA && fits16) L.bytes[h][16 * (oy - ymin) + (ox - xmin)] = 1;
-            wave_lds_sync();
-            uint64_t C0[4], C1[4];
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                const uint64_t b0 = ballot(L.bytes[h][64 * w + ll] != 0);
-                const uint64_t b1 = ballot(L.bytes[h][64 * w + 32 + ll] != 0);
-                C0[w] = (uint64_t)lo32(b0) | ((uint64_t)lo32(b1) << 32);
-                C1[w] = (uint64_t)hi32(b0) | ((uint64_t)hi32(b1) << 32);
-            }
-            if (fits0) footprint_mask_f<F>(C0, B0);
-            if (fits1) footprint_mask_f<F>(C1, B1);
+        // ---- box per half.  Mask and List only need a 16x16 window that
+        // holds every footprint of the half: try the one centred on a lane of
+        // it (the tile's middle when it is in A) before reducing the boxes.
+        int xmins[2] = {0, 0}, ymins[2] = {0, 0}, bbw[2] = {0, 0}, bbh[2] = {0, 0};
+        bool window = false;
+        if constexpr (kWindowed && !STATS) {
 #pragma unroll
             for (int hh = 0; hh < 2; ++hh) {
-                const uint64_t* Bh = hh ? B1 : B0;
-                int base = 0;
-#pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    if ((Bh[w] >> lane) & 1u) {
-                        const int r = base + mbcnt(Bh[w]);
-                        L.items[hh][r] = (uint16_t)(64 * w + lane);
-                        L.rank[hh][64 * w + lane] = (uint8_t)r;
-                    }
-                    base += popc64(Bh[w]);
+                const uint64_t m = half_mask(f.A, hh);
+                if (m) {
+                    const int mid = 32 * hh + 20;
+                    const int rl = ((m >> mid) & 1ull) ? mid : (int)__builtin_ctzll(m);
+                    xmins[hh] = __builtin_amdgcn_readlane(ox, rl) - (16 - F) / 2;
+                    ymins[hh] = __builtin_amdgcn_readlane(oy, rl) - (16 - F) / 2;
                 }
-                if (hh) nmask1 = base;
-                else nmask0 = base;
+            }
+            const uint32_t dx = (uint32_t)ox - (uint32_t)(h ? xmins[1] : xmins[0]);
+            const uint32_t dy = (uint32_t)oy - (uint32_t)(h ? ymins[1] : ymins[0]);
+            window = (ballot((dx > dy ? dx : dy) > (uint32_t)(16 - F)) & f.A) == 0;
+        }
+        bool fits[2] = {nAs[0] > 0, nAs[1] > 0};
+        if ((kCollab || STATS) && f.A && !window) {
+            int xmax[2], ymax[2];
+            halves_reduce(inA ? ox : INT32_MAX, MinOp(), xmins[0], xmins[1]);
+            halves_reduce(inA ? oy : INT32_MAX, MinOp(), ymins[0], ymins[1]);
+            halves_reduce(inA ? ox + F - 1 : INT32_MIN, MaxOp(), xmax[0], xmax[1]);
+            halves_reduce(inA ? oy + F - 1 : INT32_MIN, MaxOp(), ymax[0], ymax[1]);
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) {
+                bbw[hh] = nAs[hh] ? xmax[hh] - xmins[hh] + 1 : 0;
+                bbh[hh] = nAs[hh] ? ymax[hh] - ymins[hh] + 1 : 0;
+                if (!nAs[hh]) xmins[hh] = ymins[hh] = 0;
+                fits[hh] = nAs[hh] > 0 && bbw[hh] <= 16 && bbh[hh] <= 16;
+            }
+        }
+        const int xmin = h ? xmins[1] : xmins[0], ymin = h ? ymins[1] : ymins[0];
+        const int bw = h ? bbw[1] : bbw[0];
+        const bool fits16 = h ? fits[1] : fits[0];
+
+        // ---- distinct texels of the halves whose box fits 16x16
+        WindowSet S[2] = {{0u, 0u, 0}, {0u, 0u, 0}};
+        uint64_t B[2][4] = {{0, 0, 0, 0}, {0, 0, 0, 0}};   // tile records only
+        const int corner = inA && fits16 ? 16 * (oy - ymin) + (ox - xmin) : 0;
+        if ((kWindowed || STATS) && (fits[0] || fits[1])) {
+            window_set_halves<F>(L.window, inA && fits16, h, corner, S);
+#pragma unroll
+            for (int hh = 0; hh < 2; ++hh) {
+                if constexpr (STATS) {
+                    uint64_t C[4];
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) C[w] = ballot(L.bytes(hh)[64 * w + lane] != 0);
+                    footprint_mask_f<F>(C, B[hh]);
+                }
+                // h and h^-1 as tables
+                reinterpret_cast<uint32_t*>(L.rank[hh])[lane] = S[hh].ranks;
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if (S[hh].set & (1u << (8 * q))) L.items[hh][(S[hh].ranks >> (8 * q)) & 0xffu] = (uint8_t)(4 * lane + q);
             }
             wave_lds_sync();
         }
@@ -399,66 +372,65 @@ __global__ __launch_bounds__(kWave * kW32Waves) void k_filter_w32(FilterArgs a, 
         HalfDecision D[2];
         bool sorted = false;
         int n0s = 0, ntot = 0;
-        if constexpr (METHOD == CTF_LIST) {
-            if ((nA0 && !fits0) || (nA1 && !fits1)) {
-                ntot = w32_list_sorted<F>(L, inA, h, ox, oy, xmin, ymin, n0s);
-                sorted = true;
+        auto& seg = reinterpret_cast<SegmentScratch<F>&>(L.vals);
+        const bool any_sort = (nAs[0] && !fits[0]) || (nAs[1] && !fits[1]);
+        if constexpr (METHOD == CTF_LIST || STATS) {
+            if (any_sort) {
+                ntot = segment_sort(seg, L.first, inA && !fits16, (uint32_t)h, ox, oy, xmin, ymin, n0s);
+                sorted = METHOD == CTF_LIST;
             }
         }
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
-            const int nAh = hh ? nA1 : nA0, bw = hh ? bbw1 : bbw0, bh = hh ? bbh1 : bbh0;
-            const bool fh = hh ? fits1 : fits0;
-            const int nm = hh ? nmask1 : nmask0;
             HalfDecision& d = D[hh];
+            const int nseg = hh ? ntot - n0s : n0s;
             d.cap_ok = true;
             d.count_ok = true;
             d.success = false;
             d.n = 0;
-            d.unique = fh ? nm : 0;
+            d.unique = fits[hh] ? S[hh].n : nAs[hh] ? nseg : 0;
             if constexpr (METHOD == CTF_BOX) {
-                const int64_t area = (int64_t)bw * bh;
+                const int64_t area = (int64_t)bbw[hh] * bbh[hh];
                 d.n = area > INT32_MAX ? INT32_MAX : (int)area;
-                d.cap_ok = (a.box_w == 0 || bw <= a.box_w) && (a.box_h == 0 || bh <= a.box_h);
-                d.count_ok = area <= (int64_t)k * nAh;
-                d.success = nAh > 0 && d.cap_ok && d.count_ok;
+                d.cap_ok = (a.box_w == 0 || bbw[hh] <= a.box_w) && (a.box_h == 0 || bbh[hh] <= a.box_h);
+                d.count_ok = area <= (int64_t)k * nAs[hh];
+                d.success = nAs[hh] > 0 && d.cap_ok && d.count_ok;
             } else if constexpr (METHOD == CTF_MASK) {
-                d.cap_ok = fh;
-                d.n = fh ? nm : 0;
-                d.count_ok = d.n <= k * nAh;
-                d.success = fh && d.count_ok;
+                d.cap_ok = fits[hh];
+                d.n = fits[hh] ? S[hh].n : 0;
+                d.count_ok = d.n <= k * nAs[hh];
+                d.success = fits[hh] && d.count_ok;
             } else if constexpr (METHOD == CTF_LIST) {
-                d.n = (nAh && !fh) ? (hh ? ntot - n0s : n0s) : nm;
-                d.unique = d.n;
-                d.count_ok = d.n <= k * nAh;
-                d.success = nAh > 0 && d.count_ok;
+                d.n = d.unique;
+                d.count_ok = d.n <= k * nAs[hh];
+                d.success = nAs[hh] > 0 && d.count_ok;
             }
         }
-        if constexpr (STATS && METHOD != CTF_LIST) {
-            if ((nA0 && !fits0) || (nA1 && !fits1)) {
-                int n0u = 0;
-                const int nu = w32_list_sorted<F>(L, inA, h, ox, oy, xmin, ymin, n0u);
-                if (nA0 && !fits0) D[0].unique = n0u;
-                if (nA1 && !fits1) D[1].unique = nu - n0u;
-            }
-        }
-        if (!nA0) D[0].unique = 0;
-        if (!nA1) D[1].unique = 0;
         const int n = h ? D[1].n : D[0].n;
         const bool success = h ? D[1].success : D[0].success;
         const bool half_sorted = sorted && nA > 0 && !fits16;
-        const int key_off = h ? n0s : 0;
+        if constexpr (METHOD == CTF_LIST) {
+            if (sorted) {
+                segment_emit(seg, [&](int i, int g, int dx, int dy) {
+                    if (!(g ? D[1].success : D[0].success)) return;
+                    const int2 c = make_int2((g ? xmins[1] : xmins[0]) + dx, (g ? ymins[1] : ymins[0]) + dy);
+                    L.half[g].list[i - (g ? n0s : 0)] = c;
+                });
+                wave_lds_sync();
+            }
+        }
 
+        const bool active = lane_in(f.act);
         bool exact, draws;
         if constexpr (METHOD == CTF_BILINEAR4) {
-            exact = f.active;
+            exact = active;
             draws = false;
         } else if constexpr (METHOD == CTF_STF1) {
             exact = false;
-            draws = f.active;
+            draws = active;
         } else {
             exact = inA && success;
-            draws = f.active && !exact;
+            draws = active && !exact;
         }
         const uint64_t stfw = ballot(draws);
 
@@ -466,9 +438,14 @@ __global__ __launch_bounds__(kWave * kW32Waves) void k_filter_w32(FilterArgs a, 
         float4 res = make_float4(0.f, 0.f, 0.f, 0.f);
         int2 pick = make_int2(INT32_MIN, INT32_MIN);
         uint32_t h1 = 0, h2 = 0;
+        Footprint fl;
+        fl.x0 = f.x0;
+        fl.y0 = f.y0;
+        fl.s = f.s;
+        fl.t = f.t;
         if (draws) {
             stf_hashes(a.seed, a.layer, px, py, h1, h2);
-            pick = stf_pick_filter<FILTER>(f, h1, h2);
+            pick = stf_pick_filter<FILTER>(fl, h1, h2);
         }
         // fallback C / C+ for the lanes of A of a failed half
         bool fbl = false;
@@ -477,76 +454,59 @@ __global__ __launch_bounds__(kWave * kW32Waves) void k_filter_w32(FilterArgs a, 
         if constexpr (FB && kCollab) {
             fbl = !success && nA > 0;
             if (ballot(fbl) != 0)
-                P = plan_fallback_w32<FILTER, F>(L, a.fallback, fbl, inA, h, nA, rankA, f, pick, pcg_hash(h2), fits16,
-                                                  xmin, ymin, Hm, nprod0, nprod1);
+                P = plan_fallback_w32<FILTER, F>(L, a.fallback, fbl, inA, h, nA, rankA, fl, pick, pcg_hash(h2), fits16,
+                                                  xmin, ymin, half_mask(~0ull, h), nprod0, nprod1);
         }
         if constexpr (METHOD == CTF_BILINEAR4) {
             if (exact) res = full_filter<FILTER, TEX>(T, terms_lds, joint, f.s, f.t, ox, oy, texel);
         } else {
             for (int round = 0; round < (kCollab ? k : 1); ++round) {
+                // round 0 also evaluates the one-tap draws and the texels a
+                // failed half planned, in the same pass as the other half's
                 const int item = rankA + round * nA;
                 const bool produce = kCollab && success && inA && item < n;
+                const bool planned = FB && kCollab && round == 0 && fbl && inA && P.produces;
                 const bool draw_now = draws && round == 0 && !(fbl && inA);
-                if (ballot(produce || draw_now) == 0) break;
-                int ex = pick.x, ey = pick.y;
+                if (ballot(produce || draw_now || planned) == 0) break;
+                int2 e = planned ? P.texel : pick;
                 if (produce) {
                     if constexpr (METHOD == CTF_BOX) {
-                        ex = xmin + item % bbw;
-                        ey = ymin + item / bbw;
+                        e = make_int2(xmin + item % bw, ymin + item / bw);
+                    } else if (half_sorted) {
+                        e = L.half[h].list[item];
                     } else {
-                        if (half_sorted) {
-                            const uint64_t key = L.keys[key_off + item];
-                            ex = xmin + (int)(uint32_t)key;
-                            ey = ymin + (int)((key >> 32) & 0x3fffffffu);
-                        } else {
-                            const int t = L.items[h][item];
-                            ex = xmin + (t & 15);
-                            ey = ymin + (t >> 4);
-                        }
+                        const int t = L.items[h][item];
+                        e = make_int2(xmin + (t & 15), ymin + (t >> 4));
                     }
-                    if (STATS && a.lists) reinterpret_cast<int2*>(a.lists)[(size_t)tile * kMaxItems + item] = make_int2(ex, ey);
+                    if (STATS && a.lists) reinterpret_cast<int2*>(a.lists)[(size_t)tile * kMaxItems + item] = e;
                 }
-                if (produce || draw_now) {
-                    const float4 v = texel(ex, ey);
-                    if (produce) L.vals[h][item] = v;
+                if (produce || draw_now || planned) {
+                    const float4 v = texel(e.x, e.y);
+                    if (produce || planned) L.vals[h][produce ? item : P.slot] = v;
                     if (draw_now) res = v;
                 }
             }
-            if constexpr (FB && kCollab) {
-                // the fallback halves' planned texels, then Eq. 1
-                if (fbl && inA && P.produces) L.vals[h][P.slot] = texel(P.texel.x, P.texel.y);
-                wave_lds_sync();
-                if (fbl && inA) res = fallback_color_w32<FILTER, F>(L, P, h, h ? nprod1 : nprod0, f, pick, xmin, ymin);
-            }
             if constexpr (kCollab) {
                 wave_lds_sync();
+                if (FB && fbl && inA)
+                    res = fallback_color_w32<FILTER, F>(L, P, h, h ? nprod1 : nprod0, fl, pick, xmin, ymin);
                 if (exact) {
-                    // item index of tap (i, j) of this half's list
-                    auto item_of = [&](int i, int j) -> int {
-                        if constexpr (METHOD == CTF_BOX) {
-                            return (ox + i - xmin) + (oy + j - ymin) * bbw;
-                        } else {
-                            if (half_sorted) {
-                                const uint64_t key = ((uint64_t)h << 62) |
-                                                     ((uint64_t)(uint32_t)(oy + j - ymin) << 32) |
-                                                     (uint32_t)(ox + i - xmin);
-                                return w32_find<F>(L, key_off, key_off + n, key) - key_off;
-                            }
-                            return L.rank[h][16 * (oy + j - ymin) + (ox + i - xmin)];
-                        }
+                    // first item of footprint row j; the row's other taps follow
+                    auto row_item = [&](int j) -> int {
+                        if constexpr (METHOD == CTF_BOX) return (ox - xmin) + (oy + j - ymin) * bw;
+                        else return half_sorted ? L.first[F * lane + j] : L.rank[h][corner + 16 * j];
                     };
                     if constexpr (F == 2) {
-                        res = bilerp(f.s, f.t, L.vals[h][item_of(0, 0)], L.vals[h][item_of(1, 0)],
-                                     L.vals[h][item_of(0, 1)], L.vals[h][item_of(1, 1)]);
+                        const float4 *v0 = L.vals[h] + row_item(0), *v1 = L.vals[h] + row_item(1);
+                        res = bilerp(f.s, f.t, v0[0], v0[1], v1[0], v1[1]);
                     } else {
                         float wx[4], wy[4];
                         taps32<FILTER>(f.s, wx);
                         taps32<FILTER>(f.t, wy);
 #pragma unroll
                         for (int j = 0; j < 4; ++j) {
-                            const float4 r = row4(wx, L.vals[h][item_of(0, j)], L.vals[h][item_of(1, j)],
-                                                  L.vals[h][item_of(2, j)], L.vals[h][item_of(3, j)]);
-                            res = col_acc(wy[j], r, res, j == 0);
+                            const float4* const v = L.vals[h] + row_item(j);
+                            res = col_acc(wy[j], row4(wx, v[0], v[1], v[2], v[3]), res, j == 0);
                         }
                     }
                 }
@@ -554,14 +514,25 @@ __global__ __launch_bounds__(kWave * kW32Waves) void k_filter_w32(FilterArgs a, 
         }
 
         // ---- outputs, per-tile records (lanes 0 and 32), frame counters
-        if (in_screen) {
-            reinterpret_cast<float4*>(a.out)[pix] = res;
-            if (a.stf_xy)
-                reinterpret_cast<int2*>(a.stf_xy)[pix] = draws ? pick : make_int2(INT32_MIN, INT32_MIN);
+        {
+            // unconditional: a lane off the screen repeats its tile's first
+            // pixel, the pair's first tile if its own is past the last
+            const int src = h && !tile_ok ? 0 : lane & 32;
+            auto from = [&](float v) { return __int_as_float(__builtin_amdgcn_ds_bpermute(4 * src, __float_as_int(v))); };
+            float4 o = res;
+            if (ballot(!in_screen) != 0) {
+                const float4 e = make_float4(from(res.x), from(res.y), from(res.z), from(res.w));
+                o = make_float4(in_screen ? res.x : e.x, in_screen ? res.y : e.y, in_screen ? res.z : e.z,
+                                in_screen ? res.w : e.w);
+            }
+            const int ftx = h && !tile_ok ? cur.tx : tx, fty = h && !tile_ok ? cur.ty : ty;
+            reinterpret_cast<float4*>(a.out)[in_screen ? pix : (int64_t)(fty * 4) * a.sw + ftx * 8] = o;
         }
+        if (in_screen && a.stf_xy)
+            reinterpret_cast<int2*>(a.stf_xy)[pix] = draws ? pick : make_int2(INT32_MIN, INT32_MIN);
         int evals[2];
-        const uint32_t actm[2] = {lo32(act), hi32(act)}, stfm[2] = {lo32(stfw), hi32(stfw)};
-        const uint32_t Am[2] = {lo32(Aw), hi32(Aw)};
+        const uint32_t actm[2] = {lo32(f.act), hi32(f.act)}, stfm[2] = {lo32(stfw), hi32(stfw)};
+        const uint32_t Am[2] = {lo32(f.A), hi32(f.A)};
 #pragma unroll
         for (int hh = 0; hh < 2; ++hh) {
             if constexpr (METHOD == CTF_BILINEAR4) evals[hh] = F * F * __popc(actm[hh]);
@@ -571,16 +542,15 @@ __global__ __launch_bounds__(kWave * kW32Waves) void k_filter_w32(FilterArgs a, 
         }
         if (STATS && ll == 0 && tile_ok && a.tile_stats) {
             const HalfDecision& d = D[h];
-            const uint64_t* Bh = h ? B1 : B0;
             ctf_tile_stats S;
             S.active = actm[h];
             S.part = Am[h];
             S.stf = stfm[h];
-            for (int w = 0; w < 4; ++w) S.mask[w] = fits16 ? Bh[w] : 0ull;
+            for (int w = 0; w < 4; ++w) S.mask[w] = fits16 ? B[h][w] : 0ull;
             S.xmin = xmin;
             S.ymin = ymin;
-            S.bbw = h ? bbw1 : bbw0;
-            S.bbh = h ? bbh1 : bbh0;
+            S.bbw = bbw[h];
+            S.bbh = bbh[h];
             S.n = d.n;
             S.unique = d.unique;
             S.evals = evals[h];
