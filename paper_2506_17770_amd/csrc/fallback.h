@@ -50,7 +50,7 @@ struct StashEntry {  // a lane's footprint, read by the spare lanes of C+
 
 // Plans the productions of a failed wave.  fb is CTF_FB_C or CTF_FB_CPLUS;
 // C+ falls back to C when the box exceeds 16x16.  LDS is the kernel's
-// per-wave struct; its members keys (>= 2 KB), rank and bytes (256 bytes
+// per-wave struct; its members keys (>= 2 KB), rank and byte_area() (256 bytes
 // each) are overwritten.  h3 is this lane's third hash of the draw chain.
 template <int FILTER, class LDS>
 __device__ FallbackPlan plan_fallback(LDS& L, int fb, bool inA, int nA, int rankA, const Footprint& f, int2 pick,
@@ -65,14 +65,14 @@ __device__ FallbackPlan plan_fallback(LDS& L, int fb, bool inA, int nA, int rank
         // mask S of the drawn texels
         StashEntry* stash = reinterpret_cast<StashEntry*>(L.keys);           // 64 x 16 B
         uint16_t* sitems = reinterpret_cast<uint16_t*>(L.keys + 128);       // 64 x 2 B
-        reinterpret_cast<uint32_t*>(L.bytes)[lane] = 0u;
+        reinterpret_cast<uint32_t*>(L.byte_area())[lane] = 0u;
         stash[lane] = StashEntry{f.x0, f.y0, f.s, f.t};
         wave_lds_sync();
-        if (inA) L.bytes[16 * (pick.y - ymin) + (pick.x - xmin)] = 1;
+        if (inA) L.byte_area()[16 * (pick.y - ymin) + (pick.x - xmin)] = 1;
         wave_lds_sync();
         uint64_t S[4];
 #pragma unroll
-        for (int w = 0; w < 4; ++w) S[w] = ballot(L.bytes[64 * w + lane] != 0);
+        for (int w = 0; w < 4; ++w) S[w] = ballot(L.byte_area()[64 * w + lane] != 0);
         int ns = 0;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
@@ -81,7 +81,7 @@ __device__ FallbackPlan plan_fallback(LDS& L, int fb, bool inA, int nA, int rank
         }
         wave_lds_sync();
         // lane of each rank of A (the bytes array is free after the ballots)
-        if (inA) L.bytes[rankA] = (uint8_t)lane;
+        if (inA) L.byte_area()[rankA] = (uint8_t)lane;
         wave_lds_sync();
         P.produces = false;
         if (inA && rankA < ns) {
@@ -90,7 +90,7 @@ __device__ FallbackPlan plan_fallback(LDS& L, int fb, bool inA, int nA, int rank
             P.texel = make_int2(xmin + (t & 15), ymin + (t >> 4));
         } else if (inA) {
             constexpr int F = Taps<FILTER>::F, O = Taps<FILTER>::O;
-            const StashEntry T = stash[L.bytes[cplus_target(nA, ns, rankA)]];
+            const StashEntry T = stash[L.byte_area()[cplus_target(nA, ns, rankA)]];
             float wx[4], wy[4];
             taps32<FILTER>(T.s, wx);
             taps32<FILTER>(T.t, wy);

@@ -46,6 +46,7 @@ struct DecLds {
     uint64_t keys[kMaxItems];   // fallback planning
     uint8_t rank[256];          // Mask/List: position t -> row (h^-1); List past 16x16: first item of a lane's rows
     uint8_t bytes[256];         // footprint-corner scatter before the ballots
+    __device__ uint8_t* byte_area() { return bytes; }
 };
 
 // Rows past R read whatever the row list holds there (the index is kept

@@ -29,10 +29,11 @@ template <int F>
 struct WaveLds {
     float4 vals[kMaxItems];         // produced texel values, by item index; the List's sort before any
     uint64_t keys[kMaxItems];       // List past 16x16: texel of each item (int2); fallback planning
-    uint16_t items[kMaxItems];      // Mask: item i -> mask position t = h(i, B)
+    uint32_t window[kWindowWords];  // window_set; fallback C+: byte scatter
+    uint8_t items[kMaxItems];       // Mask: item i -> mask position t = h(i, B)
     uint8_t rank[256];              // Mask: position t -> item index h^-1(t, B); List past 16x16: first items of a
                                     // lane's footprint rows
-    uint8_t bytes[256];             // Mask: footprint-corner scatter before the ballots
+    __device__ uint8_t* byte_area() { return reinterpret_cast<uint8_t*>(window + kWindowPad); }
 };
 static_assert(sizeof(SegmentScratch<4>) <= kMaxItems * sizeof(float4), "sort in vals");
 static_assert(kWavesPerBlock * sizeof(WaveLds<2>) + kLdsTermEntries * sizeof(int4) <= 32768,
@@ -65,6 +66,8 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (simt_min_waves<FILTER>()))
     const int wid = wave_in_block();
     const int lane = lane_id();
     WaveLds<F>& L = lds_all[wid];
+    if constexpr (METHOD == CTF_LIST || METHOD == CTF_MASK || STATS)
+        if (lane < kWindowPad) L.window[lane] = 0u;
     bool staged = false, split_ok = false;
     if constexpr (kStage) {
         staged = stage_terms(T, terms_lds);
@@ -112,11 +115,15 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (simt_min_waves<FILTER>()))
         const int64_t pix = (int64_t)py * a.sw + px;
 
         // ---- step 1: footprint, participation (A = active and magnifying)
-        const Footprint f = footprint(uv_cur.x, uv_cur.y, d_cur, (float)T.width, (float)T.height);
+        const WaveFootprint wf = wave_footprint(uv_cur.x, uv_cur.y, d_cur, (float)T.width, (float)T.height);
+        Footprint f;
+        f.x0 = wf.x0;
+        f.y0 = wf.y0;
+        f.s = wf.s;
+        f.t = wf.t;
         const int ox = f.x0 - O, oy = f.y0 - O;   // upper-left tap of the FxF footprint
-        const bool inA = f.active && f.magnify;
-        const uint64_t act = ballot(f.active);
-        const uint64_t A = ballot(inA);
+        const uint64_t act = wf.act, A = wf.A;
+        const bool inA = lane_in(A), active = lane_in(act);
         const int nA = popc64(A);
         const int rankA = mbcnt(A);  // edge remapping: lane of rank r produces items r, r+|A|, ...
 
@@ -134,9 +141,8 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (simt_min_waves<FILTER>()))
                 constexpr int H = (16 - F) / 2;
                 const int rl = ((A >> 36) & 1ull) ? 36 : (int)__builtin_ctzll(A);
                 const int wx = __builtin_amdgcn_readlane(ox, rl) - H, wy = __builtin_amdgcn_readlane(oy, rl) - H;
-                const bool outside =
-                    inA && ((uint32_t)(ox - wx) > (uint32_t)(16 - F) || (uint32_t)(oy - wy) > (uint32_t)(16 - F));
-                if (ballot(outside) == 0) {
+                const uint32_t dx = (uint32_t)(ox - wx), dy = (uint32_t)(oy - wy);
+                if ((ballot((dx > dy ? dx : dy) > (uint32_t)(16 - F)) & A) == 0) {
                     window = true;
                     xmin = wx;
                     ymin = wy;
@@ -153,33 +159,25 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (simt_min_waves<FILTER>()))
         }
         const bool fits16 = window || (nA > 0 && bbw <= 16 && bbh <= 16);
 
-        // ---- 16x16 wave mask B (Mask Sampling; also the exact set when it fits)
-        uint64_t B[4] = {0, 0, 0, 0};
+        // ---- distinct texels of a 16x16 window (Mask Sampling; also the
+        // exact set when the box fits), with h and h^-1 as tables
+        uint64_t B[4] = {0, 0, 0, 0};   // tile records only
         int nmask = 0;
         constexpr bool kNeedMask = METHOD == CTF_MASK || METHOD == CTF_LIST || STATS;
+        const int corner = inA ? 16 * (oy - ymin) + (ox - xmin) : 0;
         if (kNeedMask && fits16) {
-            // corners of the footprints (mask C) by one LDS byte per lane and
-            // four ballots; B = OR of C shifted over the FxF footprint
-            reinterpret_cast<uint32_t*>(L.bytes)[lane] = 0u;
-            wave_lds_sync();
-            if (inA) L.bytes[16 * (oy - ymin) + (ox - xmin)] = 1;
-            wave_lds_sync();
-            uint64_t C[4];
+            const WindowSet S = window_set<F>(L.window, inA, corner);
+            if constexpr (STATS) {
+                uint64_t C[4];
 #pragma unroll
-            for (int w = 0; w < 4; ++w) C[w] = ballot(L.bytes[64 * w + lane] != 0);
-            footprint_mask_f<F>(C, B);
-            // h and h^-1 as tables: set bit t of rank r gives items[r] = t, rank[t] = r
-            int base = 0;
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                if ((B[w] >> lane) & 1u) {
-                    const int r = base + mbcnt(B[w]);
-                    L.items[r] = (uint16_t)(64 * w + lane);
-                    L.rank[64 * w + lane] = (uint8_t)r;
-                }
-                base += popc64(B[w]);
+                for (int w = 0; w < 4; ++w) C[w] = ballot(L.byte_area()[64 * w + lane] != 0);
+                footprint_mask_f<F>(C, B);
             }
-            nmask = base;
+            reinterpret_cast<uint32_t*>(L.rank)[lane] = S.ranks;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (S.set & (1u << (8 * q))) L.items[(S.ranks >> (8 * q)) & 0xffu] = (uint8_t)(4 * lane + q);
+            nmask = S.n;
             wave_lds_sync();
         }
 
@@ -220,14 +218,14 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (simt_min_waves<FILTER>()))
         // lanes whose output is exact filtering vs a one-tap draw
         bool exact, draws;
         if constexpr (METHOD == CTF_BILINEAR4) {
-            exact = f.active;
+            exact = active;
             draws = false;
         } else if constexpr (METHOD == CTF_STF1) {
             exact = false;
-            draws = f.active;
+            draws = active;
         } else {
             exact = inA && success;
-            draws = f.active && !exact;
+            draws = active && !exact;
         }
         const uint64_t stfmask = ballot(draws);
 
@@ -327,7 +325,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (simt_min_waves<FILTER>()))
                         if constexpr (METHOD == CTF_BOX) {
                             return (ox - xmin) + (oy + j - ymin) * bbw;
                         } else {
-                            return L.rank[sorted ? F * lane + j : 16 * (oy + j - ymin) + (ox - xmin)];
+                            return L.rank[sorted ? F * lane + j : corner + 16 * j];
                         }
                     };
                     if constexpr (F == 2) {

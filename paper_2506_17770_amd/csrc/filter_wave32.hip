@@ -243,7 +243,8 @@ __global__ __launch_bounds__(kWave * kW32Waves, 4) void k_filter_w32(FilterArgs 
     const int lane = lane_id();
     const int h = lane >> 5, ll = lane & 31;
     W32Lds& L = lds_all[wid];
-    if (lane < kWindowPad) L.window[lane] = L.window[kWindowWords + lane] = 0u;
+    if constexpr (kWindowed || STATS)
+        if (lane < kWindowPad) L.window[lane] = L.window[kWindowWords + lane] = 0u;
     bool lds_float = false;
     if constexpr (kStage) lds_float = stage_terms(T, terms_lds) && T.fterms != nullptr;
     const bool joint = joint_texels(T, lds_float);
