@@ -1,7 +1,7 @@
 // decoder.hip -- learned texel producer: parameters, training kernels, C ABI.
 //
 // Float32 master parameters live on the device in the flat layout of
-// include/ctf.h.  Training steps run four kernels on one stream:
+// include/ctf.h.  Training steps run three kernels on one stream:
 //   k_sample   texel coordinates from the pcg hash of (seed, step, sample)
 //              and their targets from a texel producer;
 //   k_train    forward + backward on MFMA for 16-sample tiles (operands in
@@ -11,15 +11,18 @@
 //              sums of the MLP weight gradients (batch reductions on MFMA
 //              after an LDS transpose of each 16x16 block, the waves' sums
 //              added in LDS in a fixed order);
-//   k_reduce   fixed-order sum of the partials (deterministic) and the loss;
-//   k_adam     Adam on the master copy, rewriting the low-precision latent
+//   k_adam     fixed-order sum of the partials (deterministic) and the loss,
+//              and Adam on the master copy, rewriting the low-precision latent
 //              copy and the packed MFMA weight blocks.
+// A loss/gradient call runs k_train and then k_grad, which sums the partials
+// and converts the latent gradient.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "ctf_internal.h"
@@ -70,8 +73,8 @@ struct ctf_decoder_s {
     float* master = nullptr;   // [total]
     float* m = nullptr;        // Adam first moment [total]
     float* v = nullptr;        // Adam second moment [total]
-    float* grad = nullptr;     // [total]; the latent part is filled from glat_fx
     int64_t* glat_fx = nullptr;  // latent gradient, fixed point (2^-44 units) [mlp0]
+    bool glat_dirty = false;     // a pass added to glat_fx and nothing cleared it (a failed launch)
     int64_t step = 0;
     // low-precision training copies
     int lp_precision = -1;
@@ -193,10 +196,13 @@ __global__ void k_zero64(int64_t* __restrict__ p, int64_t n)
         p[i] = 0;
 }
 
-__global__ void k_fx_to_float(const int64_t* __restrict__ fx, int64_t n, float* __restrict__ out)
+// A latent's gradient; its sum is left at zero for the next pass (a latent
+// cell is one 64-byte line, and the lines no sample touched are not written).
+__device__ __forceinline__ float take_fx(int64_t* fx)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        out[i] = (float)fx[i] * kFxInv;
+    const int64_t v = *fx;
+    if (v != 0) *fx = 0;
+    return (float)v * kFxInv;
 }
 
 __device__ __forceinline__ int2 sample_xy(uint64_t seed, uint32_t step, int i, int tex_w)
@@ -468,18 +474,27 @@ __global__ __launch_bounds__(64 * kTrainWaves, 1) void k_train(TrainArgs a)
         ab3 += dy;
     }
 
-    // bias gradients: sum the 16 sample columns of each lane group
+    // bias gradients: sum the 16 sample columns of each lane group (the lanes
+    // of a group end with equal sums at every step, so the mirrors pair them
+    // like exclusive-or steps of 4 and 8)
+    auto row_sum = [](float v) __attribute__((always_inline)) -> float {
+        auto dpp = [](float x, auto ctrl) __attribute__((always_inline)) {
+            return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, false));
+        };
+        v += dpp(v, std::integral_constant<int, 0xB1>{});    // quad_perm [1,0,3,2]
+        v += dpp(v, std::integral_constant<int, 0x4E>{});    // quad_perm [2,3,0,1]
+        v += dpp(v, std::integral_constant<int, 0x141>{});   // row_half_mirror
+        v += dpp(v, std::integral_constant<int, 0x140>{});   // row_mirror
+        return v;
+    };
 #pragma unroll
-    for (int o = 1; o < 16; o <<= 1) {
+    for (int k = 0; k < 4; ++k) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                ab1[i][k] += __shfl_xor(ab1[i][k], o, 64);
-                ab2[i][k] += __shfl_xor(ab2[i][k], o, 64);
-            }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) ab3[k] += __shfl_xor(ab3[k], o, 64);
+        for (int i = 0; i < 4; ++i) {
+            ab1[i][k] = row_sum(ab1[i][k]);
+            ab2[i][k] = row_sum(ab2[i][k]);
+        }
+        ab3[k] = row_sum(ab3[k]);
     }
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) loss += __shfl_xor(loss, o, 64);
@@ -546,35 +561,46 @@ __global__ __launch_bounds__(64 * kTrainWaves, 1) void k_train(TrainArgs a)
     }
 }
 
-// Fixed-order sum of the per-workgroup partials (deterministic), one pass: block
-// x sums columns [32x, 32x + 32) of the [rows][mlp_count] matrix (column
-// mlp_count: the per-workgroup losses).  Thread (c, r) adds rows r, r + 32, ...
-// of column c in order; the 32 row sums are then added as a fixed tree.
-constexpr int kRedCols = 32, kRedRows = 32;
+// Sums of the per-workgroup partials.  Block x of the first
+// reduce_blocks(mlp_count) sums columns [32x, 32x + 32) of the [rows][mlp_count]
+// matrix (column mlp_count: the per-workgroup losses) in a fixed order: thread
+// (c, r) adds rows r, r + 32, ... of column c in order; the 32 row sums are
+// then added as a fixed tree.  The kernels that consume the sums do this in
+// their first blocks, beside the element-wise work on the latents in the
+// others: as a kernel of its own it kept the chip for 3.8 us of a 60 us step.
+constexpr int kRedCols = 32, kRedRows = 32, kRedThreads = kRedCols * kRedRows;
 
-__global__ __launch_bounds__(kRedCols * kRedRows) void k_reduce(const float* __restrict__ partials,
-                                                                 const float* __restrict__ loss_part, int waves,
-                                                                 int mlp_count, float* __restrict__ grad_mlp,
-                                                                 float inv_count, float* __restrict__ loss_out)
+__host__ __device__ constexpr int reduce_blocks(int mlp_count) { return (mlp_count + 1 + kRedCols - 1) / kRedCols; }
+
+struct PartialSums {
+    const float* partials;
+    const float* loss_part;
+    int rows, mlp_count;
+    float inv_count;
+    float* loss;
+};
+
+// Column p's sum, valid in the threads of row 0 (the block's first 32);
+// writes the loss from the column behind the parameters.
+__device__ __forceinline__ float column_sum(const PartialSums& S, int p)
 {
     __shared__ float part[kRedRows][kRedCols + 1];
     const int c = threadIdx.x % kRedCols, r = threadIdx.x / kRedCols;
-    const int p = blockIdx.x * kRedCols + c;
     // column p of the partials, or the losses for p == mlp_count
-    const float* col = p < mlp_count ? partials + p : loss_part;
-    const int64_t stride = p < mlp_count ? (int64_t)mlp_count : 1;
+    const float* col = p < S.mlp_count ? S.partials + p : S.loss_part;
+    const int64_t stride = p < S.mlp_count ? (int64_t)S.mlp_count : 1;
     float s = 0.f;
-    if (p <= mlp_count) {
+    if (p <= S.mlp_count) {
         // eight rows requested at a time, added in row order
         int w = r;
-        for (; w + 7 * kRedRows < waves; w += 8 * kRedRows) {
+        for (; w + 7 * kRedRows < S.rows; w += 8 * kRedRows) {
             float x[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) x[u] = col[(int64_t)(w + u * kRedRows) * stride];
 #pragma unroll
             for (int u = 0; u < 8; ++u) s += x[u];
         }
-        for (; w < waves; w += kRedRows) s += col[(int64_t)w * stride];
+        for (; w < S.rows; w += kRedRows) s += col[(int64_t)w * stride];
     }
     part[r][c] = s;
     __syncthreads();
@@ -583,17 +609,30 @@ __global__ __launch_bounds__(kRedCols * kRedRows) void k_reduce(const float* __r
         if (r < h) part[r][c] += part[r + h][c];
         __syncthreads();
     }
-    if (r == 0) {
-        if (p < mlp_count) grad_mlp[p] = part[0][c];
-        else if (p == mlp_count && loss_out) loss_out[0] = part[0][c] * inv_count;
+    if (r == 0 && p == S.mlp_count && S.loss) S.loss[0] = part[0][c] * S.inv_count;
+    return part[0][c];
+}
+
+// The gradient of a loss/gradient call.
+__global__ __launch_bounds__(kRedThreads) void k_grad(PartialSums S, int64_t* __restrict__ glat_fx, int64_t mlp0,
+                                                      float* __restrict__ grad)
+{
+    const int red = reduce_blocks(S.mlp_count);
+    if ((int)blockIdx.x < red) {
+        const int p = (int)blockIdx.x * kRedCols + (int)threadIdx.x % kRedCols;
+        const float g = column_sum(S, p);
+        if (threadIdx.x < kRedCols && p < S.mlp_count) grad[mlp0 + p] = g;
+        return;
     }
+    const int64_t step = (int64_t)(gridDim.x - red) * kRedThreads;
+    for (int64_t i = (int64_t)(blockIdx.x - red) * kRedThreads + threadIdx.x; i < mlp0; i += step)
+        grad[i] = take_fx(glat_fx + i);
 }
 
 struct AdamArgs {
     float* master;
     float* m;
     float* v;
-    const float* grad;        // MLP part (p >= mlp0)
     int64_t* glat_fx;   // latent part, fixed point
     int64_t total, mlp0;
     int hidden;
@@ -603,34 +642,49 @@ struct AdamArgs {
     float* bias_c;
 };
 
-template <int P, bool UPDATE>
-__global__ void k_adam(AdamArgs a)
+__device__ __forceinline__ float adam_update(const AdamArgs& a, int64_t p, float gr)
+{
+    const float m = __builtin_fmaf(a.b1, a.m[p], (1.f - a.b1) * gr);
+    const float v = __builtin_fmaf(a.b2, a.v[p], (1.f - a.b2) * gr * gr);
+    a.m[p] = m;
+    a.v[p] = v;
+    const float mh = m / a.bc1, vh = v / a.bc2;
+    const float th = a.master[p] - a.lr * mh / (__builtin_sqrtf(vh) + a.eps);
+    a.master[p] = th;
+    return th;
+}
+
+template <int P>
+__device__ __forceinline__ void pack_mlp_param(const AdamArgs& a, int rel, float th)
+{
+    const uint16_t lp = Mfma<P>::cvt(th);
+    packed_visit(rel, a.hidden, [&](int q) { a.w_lp[q] = lp; }, [&](int q) { a.bias_c[q] = th; });
+}
+
+// One Adam step: the first blocks sum the partials of 32 MLP parameters each
+// and update them, the others update a latent per thread.
+template <int P>
+__global__ __launch_bounds__(kRedThreads) void k_adam(AdamArgs a, PartialSums S)
+{
+    const int red = reduce_blocks(S.mlp_count);
+    if ((int)blockIdx.x < red) {
+        const int p = (int)blockIdx.x * kRedCols + (int)threadIdx.x % kRedCols;
+        const float g = column_sum(S, p);
+        if (threadIdx.x < kRedCols && p < S.mlp_count) pack_mlp_param<P>(a, p, adam_update(a, a.mlp0 + p, g));
+        return;
+    }
+    const int64_t p = (int64_t)(blockIdx.x - red) * kRedThreads + threadIdx.x;
+    if (p < a.mlp0) a.lat_lp[p] = Mfma<P>::cvt(adam_update(a, p, take_fx(a.glat_fx + p)));
+}
+
+// Rewrites the low-precision copies from the master.
+template <int P>
+__global__ void k_pack(AdamArgs a)
 {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= a.total) return;
-    float th = a.master[p];
-    if (UPDATE) {
-        float gr;
-        if (p < a.mlp0) {
-            gr = (float)a.glat_fx[p] * kFxInv;
-            a.glat_fx[p] = 0;   // ready for the next step's sums
-        } else {
-            gr = a.grad[p];
-        }
-        const float m = __builtin_fmaf(a.b1, a.m[p], (1.f - a.b1) * gr);
-        const float v = __builtin_fmaf(a.b2, a.v[p], (1.f - a.b2) * gr * gr);
-        a.m[p] = m;
-        a.v[p] = v;
-        const float mh = m / a.bc1, vh = v / a.bc2;
-        th -= a.lr * mh / (__builtin_sqrtf(vh) + a.eps);
-        a.master[p] = th;
-    }
-    if (p < a.mlp0) {
-        a.lat_lp[p] = Mfma<P>::cvt(th);
-    } else {
-        const uint16_t lp = Mfma<P>::cvt(th);
-        packed_visit((int)(p - a.mlp0), a.hidden, [&](int q) { a.w_lp[q] = lp; }, [&](int q) { a.bias_c[q] = th; });
-    }
+    if (p < a.mlp0) a.lat_lp[p] = Mfma<P>::cvt(a.master[p]);
+    else pack_mlp_param<P>(a, (int)(p - a.mlp0), a.master[p]);
 }
 
 // ---------------------------------------------------------------------------
@@ -745,14 +799,12 @@ hipError_t ensure_batch(ctf_decoder d, int32_t n)
 
 PassScratch batch_scratch(ctf_decoder d) { return PassScratch{d->partials, d->loss_part}; }
 
-template <int P, bool UPDATE>
-hipError_t launch_adam(ctf_decoder d, float lr, hipStream_t s)
+AdamArgs adam_args(ctf_decoder d, float lr)
 {
     AdamArgs a;
     a.master = d->master;
     a.m = d->m;
     a.v = d->v;
-    a.grad = d->grad;
     a.glat_fx = d->glat_fx;
     a.total = d->lay.total;
     a.mlp0 = d->lay.mlp0;
@@ -766,8 +818,24 @@ hipError_t launch_adam(ctf_decoder d, float lr, hipStream_t s)
     a.lat_lp = d->lat_lp;
     a.w_lp = d->w_lp;
     a.bias_c = d->bias_c;
+    return a;
+}
+
+template <int P>
+hipError_t launch_adam(ctf_decoder d, float lr, const PartialSums& sums, hipStream_t s)
+{
+    const AdamArgs a = adam_args(d, lr);
+    const int64_t blocks = reduce_blocks(sums.mlp_count) + (a.mlp0 + kRedThreads - 1) / kRedThreads;
+    hipLaunchKernelGGL(k_adam<P>, dim3((unsigned)blocks), dim3(kRedThreads), 0, s, a, sums);
+    return hipGetLastError();
+}
+
+template <int P>
+hipError_t launch_pack(ctf_decoder d, hipStream_t s)
+{
+    const AdamArgs a = adam_args(d, 0.f);
     const int bs = 256;
-    hipLaunchKernelGGL((k_adam<P, UPDATE>), dim3((unsigned)((a.total + bs - 1) / bs)), dim3(bs), 0, s, a);
+    hipLaunchKernelGGL(k_pack<P>, dim3((unsigned)((a.total + bs - 1) / bs)), dim3(bs), 0, s, a);
     return hipGetLastError();
 }
 
@@ -779,24 +847,28 @@ hipError_t ensure_lp(ctf_decoder d, int precision, hipStream_t s)
     hipLaunchKernelGGL(k_fill, dim3(8), dim3(256), 0, s, reinterpret_cast<float*>(d->w_lp), (int64_t)(kAllElems / 2), 0.f);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = precision == CTF_BF16 ? launch_adam<CTF_BF16, false>(d, 0.f, s) : launch_adam<CTF_FP16, false>(d, 0.f, s);
+    e = precision == CTF_BF16 ? launch_pack<CTF_BF16>(d, s) : launch_pack<CTF_FP16>(d, s);
     if (e == hipSuccess) d->lp_precision = precision;
     return e;
 }
 
-// Loss and gradient of a batch: the MLP part lands in grad[mlp0..]; the
-// latent part in d->glat_fx (fixed point), copied to grad[0..mlp0) as float
-// when latent_to_grad is set (training reads the fixed-point sums directly).
-// zero_latent clears the fixed-point sums first; the training loop clears
-// them once and then relies on the Adam step, which zeroes what it reads.
-template <int P>
-hipError_t loss_grad_impl(ctf_decoder d, const int32_t* xy, const float* target, int32_t n,
-                          float* loss, float* grad, bool latent_to_grad, bool zero_latent,
-                          const PassScratch& sc, hipStream_t s)
+// The fixed-point latent sums are zero between calls: every pass that adds to
+// them is followed by a kernel that reads and clears them (k_grad, k_adam).
+// After a failed launch every later pass clears them first (for good: a pass
+// recorded into a graph has not run when the call returns).
+hipError_t ensure_clear(ctf_decoder d, hipStream_t s)
 {
-    const Layout& L = d->lay;
-    const int fb = 1024;
-    if (zero_latent) hipLaunchKernelGGL(k_zero64, dim3(fb), dim3(256), 0, s, d->glat_fx, L.mlp0);
+    if (!d->glat_dirty) return hipSuccess;
+    hipLaunchKernelGGL(k_zero64, dim3(1024), dim3(256), 0, s, d->glat_fx, d->lay.mlp0);
+    return hipGetLastError();
+}
+
+// Forward and backward of a batch: the MLP gradient's partial sums land in
+// sc, the latent gradient in d->glat_fx (fixed point).
+template <int P>
+hipError_t launch_train(ctf_decoder d, const int32_t* xy, const float* target, int32_t n, const PassScratch& sc,
+                        hipStream_t s)
+{
     TrainArgs a;
     a.grid = latent_grid(d->desc, d->lat_lp);
     a.w = d->w_lp;
@@ -810,15 +882,34 @@ hipError_t loss_grad_impl(ctf_decoder d, const int32_t* xy, const float* target,
     a.glat = d->glat_fx;
     a.partials = sc.partials;
     a.loss_part = sc.loss_part;
-    a.mlp_count = (int)L.mlp_count;
-    const int waves = train_waves(n);
-    hipLaunchKernelGGL((k_train<P>), dim3(waves / kTrainWaves), dim3(64 * kTrainWaves), 0, s, a);
-    const unsigned gx = (unsigned)((L.mlp_count + 1 + kRedCols - 1) / kRedCols);
-    // one partial row per workgroup (the sum of its waves' rows)
-    hipLaunchKernelGGL(k_reduce, dim3(gx), dim3(kRedCols * kRedRows), 0, s, sc.partials, sc.loss_part,
-                       waves / kTrainWaves, (int)L.mlp_count, grad + L.mlp0, 1.0f / (4.0f * (float)n), loss);
-    if (latent_to_grad) hipLaunchKernelGGL(k_fx_to_float, dim3(fb), dim3(256), 0, s, d->glat_fx, L.mlp0, grad);
+    a.mlp_count = (int)d->lay.mlp_count;
+    hipLaunchKernelGGL((k_train<P>), dim3(train_waves(n) / kTrainWaves), dim3(64 * kTrainWaves), 0, s, a);
     return hipGetLastError();
+}
+
+PartialSums partial_sums(ctf_decoder d, int32_t n, const PassScratch& sc, float* loss)
+{
+    // one partial row per workgroup (the sum of its waves' rows)
+    return PartialSums{sc.partials, sc.loss_part, train_waves(n) / kTrainWaves, (int)d->lay.mlp_count,
+                       1.0f / (4.0f * (float)n), loss};
+}
+
+template <int P>
+hipError_t loss_grad_impl(ctf_decoder d, const int32_t* xy, const float* target, int32_t n, float* loss, float* grad,
+                          const PassScratch& sc, hipStream_t s)
+{
+    hipError_t e = ensure_clear(d, s);
+    if (e != hipSuccess) return e;
+    const bool dirty = d->glat_dirty;
+    d->glat_dirty = true;
+    e = launch_train<P>(d, xy, target, n, sc, s);
+    if (e != hipSuccess) return e;
+    const PartialSums sums = partial_sums(d, n, sc, loss);
+    const int64_t red = reduce_blocks(sums.mlp_count), lat = (d->lay.mlp0 + kRedThreads - 1) / kRedThreads;
+    hipLaunchKernelGGL(k_grad, dim3((unsigned)(red + lat)), dim3(kRedThreads), 0, s, sums, d->glat_fx, d->lay.mlp0, grad);
+    e = hipGetLastError();
+    if (e == hipSuccess) d->glat_dirty = dirty;
+    return e;
 }
 
 }  // namespace
@@ -880,7 +971,7 @@ ctf_status ctf_decoder_destroy(ctf_decoder d)
 {
     if (!d) return fail(CTF_ERR_INVALID_ARG, "ctf_decoder_destroy: NULL decoder");
     DeviceScope ds(d->ctx->device);
-    for (void* p : {(void*)d->master, (void*)d->m, (void*)d->v, (void*)d->grad, (void*)d->glat_fx, (void*)d->lat_lp,
+    for (void* p : {(void*)d->master, (void*)d->m, (void*)d->v, (void*)d->glat_fx, (void*)d->lat_lp,
                     (void*)d->w_lp, (void*)d->bias_c, (void*)d->xy, (void*)d->target,
                     (void*)d->partials, (void*)d->loss_part, (void*)d->loss_tmp})
         if (p) (void)hipFree(p);
@@ -915,7 +1006,6 @@ ctf_status ctf_decoder_create(ctf_context ctx, const ctf_decoder_desc* desc, con
     hipError_t e = hipMalloc(&dec->master, bytes);
     if (e == hipSuccess) e = hipMalloc(&dec->m, bytes);
     if (e == hipSuccess) e = hipMalloc(&dec->v, bytes);
-    if (e == hipSuccess) e = hipMalloc(&dec->grad, bytes);
     if (e == hipSuccess) e = hipMalloc(&dec->glat_fx, (size_t)dec->lay.mlp0 * 8);
     if (e == hipSuccess) e = hipMalloc(&dec->lat_lp, (size_t)dec->lay.mlp0 * 2);
     if (e == hipSuccess) e = hipMalloc(&dec->w_lp, kAllElems * 2);
@@ -925,6 +1015,9 @@ ctf_status ctf_decoder_create(ctf_context ctx, const ctf_decoder_desc* desc, con
     if (e == hipSuccess) e = hipMemset(dec->m, 0, bytes);
     if (e == hipSuccess) e = hipMemset(dec->v, 0, bytes);
     if (e == hipSuccess) e = hipMemset(dec->bias_c, 0, kBiasFloats * 4);
+    if (e == hipSuccess) e = hipMemset(dec->glat_fx, 0, (size_t)dec->lay.mlp0 * 8);
+    // the fills are done before any stream of the caller's uses the decoder
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) {
         ctf_decoder_destroy(dec);
         return hip_fail(e, "ctf_decoder_create");
@@ -1017,8 +1110,8 @@ ctf_status ctf_decoder_loss_grad(ctf_decoder d, const int32_t* xy, const float* 
     hipError_t e = ensure_batch(d, n);
     if (e == hipSuccess) e = ensure_lp(d, precision, s);
     if (e == hipSuccess)
-        e = precision == CTF_BF16 ? loss_grad_impl<CTF_BF16>(d, xy, target, n, loss, grad, true, true, batch_scratch(d), s)
-                                  : loss_grad_impl<CTF_FP16>(d, xy, target, n, loss, grad, true, true, batch_scratch(d), s);
+        e = precision == CTF_BF16 ? loss_grad_impl<CTF_BF16>(d, xy, target, n, loss, grad, batch_scratch(d), s)
+                                  : loss_grad_impl<CTF_FP16>(d, xy, target, n, loss, grad, batch_scratch(d), s);
     return e == hipSuccess ? CTF_OK : hip_fail(e, "ctf_decoder_loss_grad");
 }
 
@@ -1042,8 +1135,8 @@ ctf_status ctf_decoder_loss_grad_noalloc(ctf_decoder d, const int32_t* xy, const
     const PassScratch sc{base, base + kNoAllocPartials};
     hipError_t e = ensure_lp(d, precision, s);
     if (e == hipSuccess)
-        e = precision == CTF_BF16 ? loss_grad_impl<CTF_BF16>(d, xy, target, n, loss, grad, true, true, sc, s)
-                                  : loss_grad_impl<CTF_FP16>(d, xy, target, n, loss, grad, true, true, sc, s);
+        e = precision == CTF_BF16 ? loss_grad_impl<CTF_BF16>(d, xy, target, n, loss, grad, sc, s)
+                                  : loss_grad_impl<CTF_FP16>(d, xy, target, n, loss, grad, sc, s);
     return e == hipSuccess ? CTF_OK : hip_fail(e, "ctf_decoder_loss_grad_noalloc");
 }
 
@@ -1066,9 +1159,11 @@ ctf_status ctf_decoder_train(ctf_decoder d, ctf_texture target, int64_t steps, i
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = ensure_batch(d, batch);
     if (e == hipSuccess) e = ensure_lp(d, precision, s);
+    if (e == hipSuccess && steps > 0) e = ensure_clear(d, s);
     if (e != hipSuccess) return hip_fail(e, "ctf_decoder_train: setup");
+    const PassScratch sc = batch_scratch(d);
+    const bool dirty = d->glat_dirty;
     const int sb = 256;
-    if (steps > 0) hipLaunchKernelGGL(k_zero64, dim3(1024), dim3(256), 0, s, d->glat_fx, d->lay.mlp0);
     for (int64_t it = 0; it < steps && e == hipSuccess; ++it) {
         const dim3 sg((unsigned)((batch + sb - 1) / sb));
         int2* xy = reinterpret_cast<int2*>(d->xy);
@@ -1088,13 +1183,17 @@ ctf_status ctf_decoder_train(ctf_decoder d, ctf_texture target, int64_t steps, i
         default:
             hipLaunchKernelGGL(k_sample<CTF_TEX_TABLE>, sg, dim3(sb), 0, s, T, seed, st, batch, d->desc.tex_w, xy, tg);
         }
+        e = hipGetLastError();
+        if (e != hipSuccess) break;
         float* lt = loss_trace ? loss_trace + it : d->loss_tmp;
-        e = precision == CTF_BF16
-                ? loss_grad_impl<CTF_BF16>(d, d->xy, d->target, batch, lt, d->grad, false, false, batch_scratch(d), s)
-                : loss_grad_impl<CTF_FP16>(d, d->xy, d->target, batch, lt, d->grad, false, false, batch_scratch(d), s);
+        d->glat_dirty = true;
+        e = precision == CTF_BF16 ? launch_train<CTF_BF16>(d, d->xy, d->target, batch, sc, s)
+                                  : launch_train<CTF_FP16>(d, d->xy, d->target, batch, sc, s);
         if (e != hipSuccess) break;
         d->step += 1;
-        e = precision == CTF_BF16 ? launch_adam<CTF_BF16, true>(d, lr, s) : launch_adam<CTF_FP16, true>(d, lr, s);
+        const PartialSums sums = partial_sums(d, batch, sc, lt);
+        e = precision == CTF_BF16 ? launch_adam<CTF_BF16>(d, lr, sums, s) : launch_adam<CTF_FP16>(d, lr, sums, s);
+        if (e == hipSuccess) d->glat_dirty = dirty;
     }
     return e == hipSuccess ? CTF_OK : hip_fail(e, "ctf_decoder_train");
 }
