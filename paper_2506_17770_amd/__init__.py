@@ -129,6 +129,9 @@ def _buf(t, name: str, dtype, numel: int, device: int) -> Optional[int]:
     ``numel`` elements (bytes when dtype is None).  None passes NULL."""
     if t is None:
         return None
+    if (dtype is not None and getattr(t, "is_cuda", False) and t.dtype == dtype and t.is_contiguous()
+            and t.numel() >= numel and t.device.index == device):
+        return t.data_ptr()
     if not getattr(t, "is_cuda", False):
         raise CtfError(f"{name}: expected a tensor in GPU memory")
     if t.device.index != device:
@@ -154,10 +157,14 @@ def n_tiles(sw: int, sh: int, meth: Optional[Method] = None) -> int:
     return ((sw + 7) // 8) * ((sh + th - 1) // th)
 
 
-def _stream(stream) -> Optional[int]:
-    import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream
+def _stream(stream, device: int) -> Optional[int]:
+    """Handle of ``stream``, or of the current stream of the context's device
+    (asked for by index: without one torch first looks the device up, which
+    took a quarter of a small call)."""
+    if stream is None:
+        import torch
+        stream = torch.cuda.current_stream(device)
+    return stream.cuda_stream
 
 
 def method(kind, box=(0, 0), mask_side=16, k=1, fallback=FB_STF1, filter=FILTER_BILINEAR,
@@ -242,7 +249,7 @@ class Context:
                 _buf(tile_stats, "tile_stats", None, nt * TILE_STATS_DTYPE.itemsize, dev),
                 _buf(frame_stats, "frame_stats", torch.int64, FRAME_STATS_WORDS, dev),
                 _buf(lists, "lists", i32, nt * MAX_ITEMS * 2, dev), _buf(stf, "stf", i32, npx * 2, dev))
-        _check(lib.ctf_filter(self.handle, *args, _stream(stream)))
+        _check(lib.ctf_filter(self.handle, *args, _stream(stream, dev)))
         return out
 
     def filter_layers(self, uv, duv, texs, xforms, meth: Method, seed=0, out=None, tile_stats=None,
@@ -268,7 +275,7 @@ class Context:
                 _buf(tile_stats, "tile_stats", None, n * nt * TILE_STATS_DTYPE.itemsize, dev),
                 _buf(frame_stats, "frame_stats", torch.int64, FRAME_STATS_WORDS, dev),
                 _buf(stf, "stf", i32, n * npx * 2, dev))
-        _check(lib.ctf_filter_layers(self.handle, *args, _stream(stream)))
+        _check(lib.ctf_filter_layers(self.handle, *args, _stream(stream, dev)))
         return out
 
     def decoder(self, l0, l1, hidden, tex_w, init, channels=8) -> "Decoder":
@@ -289,7 +296,7 @@ class Texture:
             out = torch.empty((n, 4), dtype=torch.float32, device=xy.device)
         dev = self.ctx.device
         _check(lib.ctf_texture_eval(self.handle, _buf(xy, "xy", torch.int32, n * 2, dev), n,
-                                    _buf(out, "out", torch.float32, n * 4, dev), _stream(stream)))
+                                    _buf(out, "out", torch.float32, n * 4, dev), _stream(stream, dev)))
         return out
 
     def close(self):
@@ -341,7 +348,7 @@ class Decoder:
         grad = torch.zeros(self.count, dtype=torch.float32, device=xy.device)
         _check(lib.ctf_decoder_loss_grad(self.handle, _buf(xy, "xy", torch.int32, n * 2, dev),
                                          _buf(target, "target", torch.float32, n * 4, dev), n,
-                                         precision, _dptr(loss), _dptr(grad), _stream(stream)))
+                                         precision, _dptr(loss), _dptr(grad), _stream(stream, dev)))
         return loss, grad
 
     def loss_grad_noalloc(self, xy, target, loss, grad, precision=BF16, stream=None):
@@ -354,14 +361,14 @@ class Decoder:
         _check(lib.ctf_decoder_loss_grad_noalloc(
             self.handle, _buf(xy, "xy", torch.int32, n * 2, dev), _buf(target, "target", torch.float32, n * 4, dev),
             n, precision, _buf(loss, "loss", torch.float32, 1, dev), _buf(grad, "grad", torch.float32, self.count, dev),
-            _stream(stream)))
+            _stream(stream, dev)))
 
     def train(self, target: Texture, steps, batch=65536, lr=1e-3, seed=0, precision=BF16,
               loss_trace=None, stream=None):
         import torch
         trace = _buf(loss_trace, "loss_trace", torch.float32, max(0, steps), self.ctx.device)
         _check(lib.ctf_decoder_train(self.handle, target.handle, steps, batch, lr,
-                                     seed & (2**64 - 1), precision, trace, _stream(stream)))
+                                     seed & (2**64 - 1), precision, trace, _stream(stream, self.ctx.device)))
 
     def close(self):
         if self.handle:

@@ -104,6 +104,7 @@ ctf_status ctf_create(int device, ctf_context* out)
     ctf_context c = new (std::nothrow) ctf_context_s;
     if (!c) return fail(CTF_ERR_OUT_OF_MEMORY, "ctf_create: host allocation");
     c->device = device;
+    c->cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     *out = c;
     return CTF_OK;
 }
@@ -271,11 +272,12 @@ static ctf_status check_method(const ctf_method* m, const char* who)
     return CTF_OK;
 }
 
-static FilterArgs filter_args(const float* uv, const float* duv, int32_t sw, int32_t sh, const ctf_method* m,
+static FilterArgs filter_args(ctf_context ctx, const float* uv, const float* duv, int32_t sw, int32_t sh, const ctf_method* m,
                               uint64_t seed, float* out, ctf_tile_stats* ts, ctf_frame_stats* fs, int32_t* lists,
                               int32_t* stf)
 {
     FilterArgs a;
+    a.cus = ctx->cus;
     a.uv = uv;
     a.duv = duv;
     a.out = out;
@@ -325,7 +327,7 @@ ctf_status ctf_filter_layers(ctf_context ctx, const float* uv, const float* uv_d
     }
     DeviceScope ds(ctx->device);
     if (ds.err != hipSuccess) return hip_fail(ds.err, "ctf_filter_layers: set device");
-    const FilterArgs a = filter_args(uv, uv_derivs, sw, sh, m, seed, out, tile_stats, frame_stats, nullptr, debug_stf);
+    const FilterArgs a = filter_args(ctx, uv, uv_derivs, sw, sh, m, seed, out, tile_stats, frame_stats, nullptr, debug_stf);
     const hipError_t e = ctf_internal_filter_layers(texs, xforms, n_layers, a, (hipStream_t)stream);
     if (e == hipErrorInvalidValue) return fail(CTF_ERR_UNSUPPORTED, "ctf_filter_layers: combination not built");
     if (e != hipSuccess) return hip_fail(e, "ctf_filter_layers: launch");
@@ -348,7 +350,7 @@ ctf_status ctf_filter(ctf_context ctx, const float* uv, const float* uv_derivs, 
     DeviceScope ds(ctx->device);
     if (ds.err != hipSuccess) return hip_fail(ds.err, "ctf_filter: set device");
 
-    const FilterArgs a = filter_args(uv, uv_derivs, sw, sh, m, seed, out, tile_stats, frame_stats, debug_lists,
+    const FilterArgs a = filter_args(ctx, uv, uv_derivs, sw, sh, m, seed, out, tile_stats, frame_stats, debug_lists,
                                      debug_stf);
     hipError_t e;
     if (m->wave_shape == CTF_WAVE_8X4 && tex->dev.kind == CTF_TEX_DECODER)

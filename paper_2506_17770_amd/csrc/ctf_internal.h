@@ -32,6 +32,7 @@ struct FilterArgs {
     ctf_frame_stats* frame_stats;
     int32_t* lists;
     int32_t* stf_xy;
+    int cus;                    // compute units of the context's device (launch sizes)
 };
 
 // Decoder parameters in the layouts the MFMA kernels read (built once per
@@ -51,6 +52,21 @@ hipError_t launch_texel_eval_simt(const DevTexture& T, const int32_t* xy, int64_
 
 void set_error(const std::string& msg);
 
+// Workgroups of kernel K (threads per workgroup, static LDS) that fit a CU;
+// queried once per kernel: the library runs on gfx950 only, so the answer is
+// one per process, and this and the compute-unit query took 0.5 us of a 4.6 us
+// call.
+template <auto K, int THREADS>
+int blocks_per_cu(int fallback)
+{
+    static const int n = [fallback] {
+        int v = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, K, THREADS, 0) != hipSuccess || v < 1) v = fallback;
+        return v;
+    }();
+    return n;
+}
+
 // Looks up the device address of the allocation-free call's scratch array
 // for `device` (which must be current); done once per device.
 hipError_t noalloc_scratch_init(int device);
@@ -59,6 +75,7 @@ hipError_t noalloc_scratch_init(int device);
 
 struct ctf_context_s {
     int device;
+    int cus;                    // compute units
 };
 
 struct ctf_decoder_s;

@@ -938,13 +938,6 @@ __global__ __launch_bounds__(64 * kDecWavesMax) void k_filter_dec_batch(FilterAr
     if (lane == 0 && a.frame_stats) fc.flush(a.frame_stats);
 }
 
-inline int device_cus()
-{
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    return cus > 0 ? cus : 256;
-}
-
 // Persistent grid: the workgroups that fill the chip with three waves per
 // SIMD, a multiple of the 8 XCDs.  Twelve waves per workgroup once every wave
 // has two tiles (see TileQueue); below, four, so that a small frame spreads
@@ -959,7 +952,7 @@ template <class Slice>
 DecLaunch dec_launch(const FilterArgs& a, int layers)
 {
     static_assert(kQueueBytes + kDecWavesMax * sizeof(Slice) <= 160 * 1024, "a workgroup's LDS");
-    const int64_t cus = device_cus();
+    const int64_t cus = a.cus;
     const int waves = a.ntiles >= 2 * cus * kDecWavesMax ? kDecWavesMax : kDecWavesMin;
     DecLaunch g;
     g.threads = 64 * waves;

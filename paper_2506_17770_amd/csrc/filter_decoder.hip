@@ -106,7 +106,7 @@ hipError_t ctf_internal_decoder_eval(const ctf_texture_s* t, const int32_t* xy, 
     if (n <= 0) return hipSuccess;
     const DevDecoderWeights& d = t->dec;
     // three waves per SIMD; 12-wave workgroups once every wave has two passes
-    const int64_t cus = device_cus(), passes = (n + 31) / 32;
+    const int64_t cus = t->ctx->cus, passes = (n + 31) / 32;
     const int waves = passes >= 2 * cus * kDecWavesMax ? kDecWavesMax : kDecWavesMin;
     int64_t blocks = (passes + waves - 1) / waves;
     if (blocks > cus * (kDecWavesMax / waves)) blocks = cus * (kDecWavesMax / waves);

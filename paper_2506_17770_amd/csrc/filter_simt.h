@@ -391,30 +391,32 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (simt_min_waves<FILTER>()))
     if (lane == 0 && a.frame_stats) fc.flush(a.frame_stats);
 }
 
+template <void (*K)(FilterArgs, DevTexture)>
+hipError_t launch_k(const FilterArgs& a, const DevTexture& T, hipStream_t s)
+{
+    // grid-stride over tiles: two rounds of the workgroups that fit on the
+    // chip at once (the second round evens out the tiles' uneven costs),
+    // several tiles per wave
+    const int64_t cap = (int64_t)a.cus * blocks_per_cu<K, kWave * kWavesPerBlock>(4) * 2;
+    int64_t blocks = (a.ntiles + kWavesPerBlock - 1) / kWavesPerBlock;
+    if (blocks > cap) blocks = cap;
+    const int64_t least = counter_min_blocks(a.ntiles, kWavesPerBlock);   // 32-bit frame counters
+    if (blocks < least) blocks = least;
+    hipLaunchKernelGGL(K, dim3((unsigned)blocks), dim3(kWave * kWavesPerBlock), 0, s, a, T);
+    return hipGetLastError();
+}
+
 template <int METHOD, int TEX, int FILTER>
 hipError_t launch_m_t(const FilterArgs& a, const DevTexture& T, hipStream_t s)
 {
     constexpr bool kCollab = METHOD == CTF_LIST || METHOD == CTF_BOX || METHOD == CTF_MASK;
     // the instantiation with statistics also writes the texel lists
     const bool st = a.tile_stats != nullptr || a.lists != nullptr;
-    void (*k)(FilterArgs, DevTexture);
     if (kCollab && a.fallback != CTF_FB_STF1)
-        k = st ? k_filter_simt<METHOD, TEX, true, FILTER, kCollab> : k_filter_simt<METHOD, TEX, false, FILTER, kCollab>;
-    else
-        k = st ? k_filter_simt<METHOD, TEX, true, FILTER, false> : k_filter_simt<METHOD, TEX, false, FILTER, false>;
-    // grid-stride over tiles: two rounds of the workgroups that fit on the
-    // chip at once (the second round evens out the tiles' uneven costs),
-    // several tiles per wave
-    int dev = 0, cus = 256, per_cu = 0;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, kWave * kWavesPerBlock, 0) != hipSuccess || per_cu < 1)
-        per_cu = 4;
-    int64_t blocks = (a.ntiles + kWavesPerBlock - 1) / kWavesPerBlock;
-    if (blocks > (int64_t)cus * per_cu * 2) blocks = (int64_t)cus * per_cu * 2;
-    const int64_t least = counter_min_blocks(a.ntiles, kWavesPerBlock);   // 32-bit frame counters
-    if (blocks < least) blocks = least;
-    hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(kWave * kWavesPerBlock), 0, s, a, T);
-    return hipGetLastError();
+        return st ? launch_k<k_filter_simt<METHOD, TEX, true, FILTER, kCollab>>(a, T, s)
+                  : launch_k<k_filter_simt<METHOD, TEX, false, FILTER, kCollab>>(a, T, s);
+    return st ? launch_k<k_filter_simt<METHOD, TEX, true, FILTER, false>>(a, T, s)
+              : launch_k<k_filter_simt<METHOD, TEX, false, FILTER, false>>(a, T, s);
 }
 
 template <int TEX, int FILTER>

@@ -573,11 +573,9 @@ __global__ __launch_bounds__(kWave * kW32Waves, 4) void k_filter_w32(FilterArgs 
 template <int METHOD, int TEX, int FILTER>
 hipError_t launch_w32_m_t(const FilterArgs& a, const DevTexture& T, hipStream_t s)
 {
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     const int64_t npairs = (a.ntiles + 1) / 2;
     int64_t blocks = (npairs + kW32Waves - 1) / kW32Waves;
-    if (blocks > (int64_t)cus * 8) blocks = (int64_t)cus * 8;
+    if (blocks > (int64_t)a.cus * 8) blocks = (int64_t)a.cus * 8;
     const int64_t least = counter_min_blocks(a.ntiles, kW32Waves);   // 32-bit frame counters
     if (blocks < least) blocks = least;
     const dim3 grid((unsigned)blocks), block(kWave * kW32Waves);
