@@ -35,7 +35,7 @@ namespace dec {
 
 // Waves of a workgroup: a whole CU's worth (three per SIMD, the occupancy the
 // kernels' registers allow) on a large frame, four on a small one
-// (dec_launch).  Each wave has a slice of the dynamic LDS behind the queues.
+// (dec_waves).  Each wave has a slice of the dynamic LDS behind the queues.
 constexpr int kDecWavesMax = 12, kDecWavesMin = 4;
 
 constexpr bool collaborative(int m) { return m == CTF_LIST || m == CTF_BOX || m == CTF_MASK; }
@@ -610,7 +610,10 @@ __global__ __launch_bounds__(64 * kDecWavesMax) void k_filter_dec(FilterArgs a, 
 // (at most 256 rows), decodes them in one pass and gathers the tiles, so the
 // pass's start-up and its partial last MFMA tile are shared.  A planned
 // tile's per-lane state waits in LDS until its gather, so no two tiles' state
-// is live in registers.
+// is live in registers.  Bound by issue: at 3840x2160 a List tile takes about
+// 307 VALU and 220 scalar instructions to plan, besides its rows' MFMA.
+// Against one tile per pass: B-spline List 299 -> 184 us, six layers 1120 ->
+// 880 us; against two tiles and bitonic sets, bilinear List 162 -> 135 us.
 // ---------------------------------------------------------------------------
 
 // Tiles per batch, measured at 3840x2160 with 2, 3, 4: bilinear List 139.7,
@@ -938,10 +941,18 @@ __global__ __launch_bounds__(64 * kDecWavesMax) void k_filter_dec_batch(FilterAr
     if (lane == 0 && a.frame_stats) fc.flush(a.frame_stats);
 }
 
+// Waves of a workgroup for n units of work (tiles, or 32-texel passes): twelve
+// from seven units per CU, four below.  A large workgroup's waves share the
+// work of their CU through one counter (see TileQueue); four-wave workgroups
+// spread a small frame over all CUs, but a CU may get one or three of them.
+// Fp16 frames, four and twelve waves (us): 384x256 (6 tiles per CU) List 11.7,
+// 12.0, 4-tap 10.6, 13.1; 384x320 (7.5) 13.1, 12.6 and 16.8, 15.9; 640x480
+// (18.8) 16.0, 15.4 and 24.0, 20.8; 1280x720 25.5, 23.4 and 54.5, 50.6; texel
+// evaluation is within 4 % either way.
+inline int dec_waves(int64_t n, int64_t cus) { return n >= 7 * cus ? kDecWavesMax : kDecWavesMin; }
+
 // Persistent grid: the workgroups that fill the chip with three waves per
-// SIMD, a multiple of the 8 XCDs.  Twelve waves per workgroup once every wave
-// has two tiles (see TileQueue); below, four, so that a small frame spreads
-// over all CUs.
+// SIMD, a multiple of the 8 XCDs.
 struct DecLaunch {
     int threads;
     int64_t blocks;
@@ -953,7 +964,7 @@ DecLaunch dec_launch(const FilterArgs& a, int layers)
 {
     static_assert(kQueueBytes + kDecWavesMax * sizeof(Slice) <= 160 * 1024, "a workgroup's LDS");
     const int64_t cus = a.cus;
-    const int waves = a.ntiles >= 2 * cus * kDecWavesMax ? kDecWavesMax : kDecWavesMin;
+    const int waves = dec_waves(a.ntiles, cus);
     DecLaunch g;
     g.threads = 64 * waves;
     g.blocks = (a.ntiles + waves - 1) / waves;

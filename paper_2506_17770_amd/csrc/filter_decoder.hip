@@ -105,9 +105,9 @@ hipError_t ctf_internal_decoder_eval(const ctf_texture_s* t, const int32_t* xy, 
 {
     if (n <= 0) return hipSuccess;
     const DevDecoderWeights& d = t->dec;
-    // three waves per SIMD; 12-wave workgroups once every wave has two passes
+    // three waves per SIMD
     const int64_t cus = t->ctx->cus, passes = (n + 31) / 32;
-    const int waves = passes >= 2 * cus * kDecWavesMax ? kDecWavesMax : kDecWavesMin;
+    const int waves = dec_waves(passes, cus);
     int64_t blocks = (passes + waves - 1) / waves;
     if (blocks > cus * (kDecWavesMax / waves)) blocks = cus * (kDecWavesMax / waves);
     const dim3 block(64 * waves);

@@ -9,7 +9,12 @@
 //
 // Half-wave quantities are computed for both halves as scalars (ballots
 // split into their 32-bit halves, DPP reductions combined per pair of
-// 16-lane rows) and each lane selects its own half's value.
+// 16-lane rows) and each lane selects its own half's value.  Texels are
+// evaluated once for the wave, whatever the halves decided: a half that
+// succeeded and one that fell back fill the lanes of the same rounds, the
+// terms come from the workgroup's LDS and the next pair's inputs are
+// requested a pair ahead (Mask with C+ at 1920x1080, 32 terms: 95 -> 73 us,
+// bound by the texel evaluations and the chain of LDS steps of a tile).
 #include "ctf_device.h"
 #include "ctf_internal.h"
 #include "fallback.h"
