@@ -344,8 +344,9 @@ class Decoder:
         if xy.dim() != 2 or xy.shape[1] != 2:
             raise CtfError("xy must be [n][2]")
         n, dev = xy.shape[0], self.ctx.device
-        loss = torch.zeros(1, dtype=torch.float32, device=xy.device)
-        grad = torch.zeros(self.count, dtype=torch.float32, device=xy.device)
+        # the call writes every element: the gradient of each parameter, the loss
+        loss = torch.empty(1, dtype=torch.float32, device=xy.device)
+        grad = torch.empty(self.count, dtype=torch.float32, device=xy.device)
         _check(lib.ctf_decoder_loss_grad(self.handle, _buf(xy, "xy", torch.int32, n * 2, dev),
                                          _buf(target, "target", torch.float32, n * 4, dev), n,
                                          precision, _dptr(loss), _dptr(grad), _stream(stream, dev)))
