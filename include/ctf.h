@@ -302,7 +302,12 @@ ctf_status ctf_decoder_set_state(ctf_decoder dec, const void *host, size_t bytes
  * [1]; grad: device float [param_count] (flat layout).
  * The first call with a larger n than any before grows the decoder's batch
  * buffers (a device allocation); calls on one decoder share those buffers
- * and must not overlap. */
+ * and must not overlap.
+ * A decoder holds the fixed-point sums of its latent gradients, which every
+ * pass (this call, its allocation-free form, a training step) leaves at zero,
+ * also one that fails.  Where not even the fill could be enqueued after a
+ * failed launch, the next call clears them; run one before replaying a graph
+ * that was recorded earlier. */
 ctf_status ctf_decoder_loss_grad(ctf_decoder dec, const int32_t *xy, const float *target,
                                  int32_t n, int32_t precision, float *loss, float *grad,
                                  void *stream);
@@ -321,7 +326,7 @@ ctf_status ctf_decoder_loss_grad(ctf_decoder dec, const int32_t *xy, const float
  * partial sums of one pass over at most CTF_NOALLOC_MAX_SAMPLES samples of a
  * decoder with hidden width <= 64), instead of the decoder's batch buffers.
  * Every call on a device uses that device's one array and each pass writes
- * every scratch entry it reads, so nothing carries over from an earlier
+ * every scratch entry it reads, so nothing in it carries over from an earlier
  * call; calls that overlap on one device (other streams, other threads,
  * other decoders) race on the array and must be serialised by the caller.
  * Errors: CTF_ERR_INVALID_ARG (NULL buffers, n <= 0 or n above

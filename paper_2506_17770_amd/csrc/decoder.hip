@@ -74,7 +74,7 @@ struct ctf_decoder_s {
     float* m = nullptr;        // Adam first moment [total]
     float* v = nullptr;        // Adam second moment [total]
     int64_t* glat_fx = nullptr;  // latent gradient, fixed point (2^-44 units) [mlp0]
-    bool glat_dirty = false;     // a pass added to glat_fx and nothing cleared it (a failed launch)
+    bool glat_dirty = false;     // a pass added to glat_fx and nothing could be enqueued to clear it
     int64_t step = 0;
     // low-precision training copies
     int lp_precision = -1;
@@ -853,15 +853,36 @@ hipError_t ensure_lp(ctf_decoder d, int precision, hipStream_t s)
     return e;
 }
 
-// The fixed-point latent sums are zero between calls: every pass that adds to
-// them is followed by a kernel that reads and clears them (k_grad, k_adam).
-// After a failed launch every later pass clears them first (for good: a pass
-// recorded into a graph has not run when the call returns).
+hipError_t launch_clear(ctf_decoder d, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_zero64, dim3(1024), dim3(256), 0, s, d->glat_fx, d->lay.mlp0);
+    return hipGetLastError();
+}
+
+// The fixed-point latent sums are zero between calls, for the calls that follow
+// and for the graphs that were recorded before: a pass that adds to them is
+// followed by a kernel that reads and clears them (k_grad, k_adam), or, if that
+// launch fails, by a fill (recover).  Should the fill fail too, the next pass
+// clears them first.  (A fill before every pass took 5 us of an eager and 10 us
+// of a recorded pass of 40.)
 hipError_t ensure_clear(ctf_decoder d, hipStream_t s)
 {
     if (!d->glat_dirty) return hipSuccess;
-    hipLaunchKernelGGL(k_zero64, dim3(1024), dim3(256), 0, s, d->glat_fx, d->lay.mlp0);
-    return hipGetLastError();
+    const hipError_t e = launch_clear(d, s);
+    // a fill that is only recorded has not run
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (e == hipSuccess && hipStreamIsCapturing(s, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone)
+        d->glat_dirty = false;
+    return e;
+}
+
+// After a pass whose launches failed with e, possibly behind k_train: an error
+// that an earlier call left to this thread is reported by the first check, when
+// k_train is on its way.
+hipError_t recover(ctf_decoder d, hipStream_t s, hipError_t e)
+{
+    if (launch_clear(d, s) != hipSuccess) d->glat_dirty = true;
+    return e;
 }
 
 // Forward and backward of a batch: the MLP gradient's partial sums land in
@@ -901,16 +922,13 @@ hipError_t loss_grad_impl(ctf_decoder d, const int32_t* xy, const float* target,
 {
     hipError_t e = ensure_clear(d, s);
     if (e != hipSuccess) return e;
-    const bool dirty = d->glat_dirty;
-    d->glat_dirty = true;
     e = launch_train<P>(d, xy, target, n, sc, s);
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess) return recover(d, s, e);
     const PartialSums sums = partial_sums(d, n, sc, loss);
     const int64_t red = reduce_blocks(sums.mlp_count), lat = (d->lay.mlp0 + kRedThreads - 1) / kRedThreads;
     hipLaunchKernelGGL(k_grad, dim3((unsigned)(red + lat)), dim3(kRedThreads), 0, s, sums, d->glat_fx, d->lay.mlp0, grad);
     e = hipGetLastError();
-    if (e == hipSuccess) d->glat_dirty = dirty;
-    return e;
+    return e == hipSuccess ? e : recover(d, s, e);
 }
 
 }  // namespace
@@ -1163,7 +1181,6 @@ ctf_status ctf_decoder_train(ctf_decoder d, ctf_texture target, int64_t steps, i
     if (e == hipSuccess && steps > 0) e = ensure_clear(d, s);
     if (e != hipSuccess) return hip_fail(e, "ctf_decoder_train: setup");
     const PassScratch sc = batch_scratch(d);
-    const bool dirty = d->glat_dirty;
     const int sb = 256;
     for (int64_t it = 0; it < steps && e == hipSuccess; ++it) {
         const dim3 sg((unsigned)((batch + sb - 1) / sb));
@@ -1187,14 +1204,16 @@ ctf_status ctf_decoder_train(ctf_decoder d, ctf_texture target, int64_t steps, i
         e = hipGetLastError();
         if (e != hipSuccess) break;
         float* lt = loss_trace ? loss_trace + it : d->loss_tmp;
-        d->glat_dirty = true;
         e = precision == CTF_BF16 ? launch_train<CTF_BF16>(d, d->xy, d->target, batch, sc, s)
                                   : launch_train<CTF_FP16>(d, d->xy, d->target, batch, sc, s);
-        if (e != hipSuccess) break;
+        if (e != hipSuccess) {
+            e = recover(d, s, e);
+            break;
+        }
         d->step += 1;
         const PartialSums sums = partial_sums(d, batch, sc, lt);
         e = precision == CTF_BF16 ? launch_adam<CTF_BF16>(d, lr, sums, s) : launch_adam<CTF_FP16>(d, lr, sums, s);
-        if (e == hipSuccess) d->glat_dirty = dirty;
+        if (e != hipSuccess) e = recover(d, s, e);
     }
     return e == hipSuccess ? CTF_OK : hip_fail(e, "ctf_decoder_train");
 }
