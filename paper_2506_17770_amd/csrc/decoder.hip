@@ -844,6 +844,7 @@ hipError_t launch_pack(ctf_decoder d, hipStream_t s)
 hipError_t ensure_lp(ctf_decoder d, int precision, hipStream_t s)
 {
     if (d->lp_precision == precision) return hipSuccess;
+    d->lp_precision = -1;   // the copies hold neither until the last launch is on its way
     // a fill kernel rather than a memset node, so the call can be captured
     hipLaunchKernelGGL(k_fill, dim3(8), dim3(256), 0, s, reinterpret_cast<float*>(d->w_lp), (int64_t)(kAllElems / 2), 0.f);
     hipError_t e = hipGetLastError();

@@ -46,7 +46,7 @@ def record(G, dec, xy, tg, prec):
     return graph, loss, grad
 
 
-def fail_after_the_backward_kernel(G, dec, xy, tg, prec):
+def failing_pass(G, dec, xy, tg, prec):
     ctf, ctx, torch = G
     torch.cuda.synchronize()
     assert ctf.lib.hipSetDevice(1 << 20) != 0       # refused by the host; the error stays with the thread
@@ -66,13 +66,13 @@ def test_replay_after_a_failed_pass(G, n, prec):
     want2 = dec.loss_grad(xy2, tg2, precision=prec)
     graph, loss, grad = record(G, dec, xy, tg, prec)
     for _ in range(2):
-        fail_after_the_backward_kernel(G, dec, xy2, tg2, prec)
+        failing_pass(G, dec, xy2, tg2, prec)
         for _ in range(2):                          # the replay next to the failure, and one after it
             loss.zero_(), grad.zero_()
             graph.replay()
             assert torch.equal(loss, want[0]) and torch.equal(grad, want[1])
         # an eager pass next to the failure, and one after it
-        fail_after_the_backward_kernel(G, dec, xy, tg, prec)
+        failing_pass(G, dec, xy, tg, prec)
         for _ in range(2):
             got = dec.loss_grad(xy2, tg2, precision=prec)
             assert torch.equal(got[0], want2[0]) and torch.equal(got[1], want2[1])
@@ -97,3 +97,17 @@ def test_first_pass_recorded(G, prec):
         assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
     for d in (dec, other):
         d.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_failed_change_of_precision(G, prec):
+    """A call in the other precision that fails while it rewrites the 16-bit
+    copies leaves no half-written copies behind."""
+    ctf, ctx, torch = G
+    dec = decoder(ctx)
+    xy, tg = batch(torch, 300, 5)
+    want = dec.loss_grad(xy, tg, precision=prec)
+    failing_pass(G, dec, xy, tg, 1 - prec)
+    got = dec.loss_grad(xy, tg, precision=prec)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    dec.close()
