@@ -86,17 +86,20 @@ struct Footprint {
 };
 
 // No branches: a NaN or infinite u or v leaves fx or fy NaN or infinite, so
-// the range test alone decides `active`, and the other members of an
-// inactive lane are unused values.
+// the range test alone decides `active`.  A coordinate out of range is not
+// converted: its x0 or y0 is 0 (the conversion would be undefined, and the
+// wave-wide tests read every lane's x0 and y0 before they mask them).  The
+// other members of an inactive lane are unused values.
 __device__ __forceinline__ Footprint footprint(float u, float v, float4 d, float W, float H)
 {
     Footprint f;
     const float fx = __builtin_fmaf(u, W, -0.5f);
     const float fy = __builtin_fmaf(v, H, -0.5f);
-    f.active = __builtin_fabsf(fx) < kRange && __builtin_fabsf(fy) < kRange;
+    const bool inx = __builtin_fabsf(fx) < kRange, iny = __builtin_fabsf(fy) < kRange;
+    f.active = inx && iny;
     const float flx = __builtin_floorf(fx), fly = __builtin_floorf(fy);
-    f.x0 = (int)flx;
-    f.y0 = (int)fly;
+    f.x0 = (int)(inx ? flx : 0.0f);
+    f.y0 = (int)(iny ? fly : 0.0f);
     f.s = fx - flx;
     f.t = fy - fly;
     const float a = d.x * W, b = d.y * H, c = d.z * W, e = d.w * H;
@@ -120,10 +123,11 @@ __device__ __forceinline__ WaveFootprint wave_footprint(float u, float v, float4
     WaveFootprint f;
     const float fx = __builtin_fmaf(u, W, -0.5f);
     const float fy = __builtin_fmaf(v, H, -0.5f);
-    f.act = ballot(__builtin_fabsf(fx) < kRange) & ballot(__builtin_fabsf(fy) < kRange);
+    const bool inx = __builtin_fabsf(fx) < kRange, iny = __builtin_fabsf(fy) < kRange;
+    f.act = ballot(inx) & ballot(iny);
     const float flx = __builtin_floorf(fx), fly = __builtin_floorf(fy);
-    f.x0 = (int)flx;
-    f.y0 = (int)fly;
+    f.x0 = (int)(inx ? flx : 0.0f);
+    f.y0 = (int)(iny ? fly : 0.0f);
     f.s = fx - flx;
     f.t = fy - fly;
     const float a = d.x * W, b = d.y * H, c = d.z * W, e = d.w * H;
