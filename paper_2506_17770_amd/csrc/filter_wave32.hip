@@ -15,6 +15,8 @@
 // terms come from the workgroup's LDS and the next pair's inputs are
 // requested a pair ahead (Mask with C+ at 1920x1080, 32 terms: 95 -> 73 us,
 // bound by the texel evaluations and the chain of LDS steps of a tile).
+#include <type_traits>
+
 #include "ctf_device.h"
 #include "ctf_internal.h"
 #include "fallback.h"
@@ -232,15 +234,28 @@ struct HalfDecision {
     bool cap_ok, count_ok, success;
 };
 
-// Five instructions per term need the terms in vector registers (from LDS by
-// broadcast: a vector instruction reads one scalar register); with the LDS
-// slices and the staged terms four workgroups fit a CU.
-template <int METHOD, int TEX, bool STATS, int FILTER, bool FB>
+// Whether a collaborative launch reads its sinusoid terms from LDS.  Five
+// instructions per term need them in vector registers, from LDS by broadcast
+// (a vector instruction reads one scalar register).  Terms that are not staged
+// as floats (more than kLdsTerms, or the integer form of textures wider than
+// 4096) are scalar loads instead: as broadcast vector loads, as in the 8x8
+// kernels, which have no scalar registers left for them, Mask at 1920x1080
+// takes 258 us in place of 131 with 70 terms and 81 in place of 64 with 16
+// integer ones.
+inline bool w32_lds_terms(const DevTexture& T)
+{
+    return T.kind == CTF_TEX_SINUSOIDS && T.fterms != nullptr && T.n_terms <= kLdsTerms;
+}
+
+// LDS_TERMS (collaborative methods): w32_lds_terms; the other methods choose
+// at run time.  With the LDS slices and the staged terms four workgroups fit a
+// CU.
+template <int METHOD, int TEX, bool STATS, int FILTER, bool FB, bool LDS_TERMS>
 __global__ __launch_bounds__(kWave * kW32Waves, 4) void k_filter_w32(FilterArgs a, DevTexture T)
 {
     constexpr int F = Taps<FILTER>::F, O = Taps<FILTER>::O;
-    constexpr bool kStage = TEX == CTF_TEX_SINUSOIDS;
     constexpr bool kCollab = METHOD == CTF_LIST || METHOD == CTF_BOX || METHOD == CTF_MASK;
+    constexpr bool kStage = TEX == CTF_TEX_SINUSOIDS && (!kCollab || LDS_TERMS);
     constexpr bool kWindowed = METHOD == CTF_LIST || METHOD == CTF_MASK;
     __shared__ W32Lds lds_all[kW32Waves];
     __shared__ int4 terms_lds[kStage ? kLdsTermEntries : 1];
@@ -251,10 +266,11 @@ __global__ __launch_bounds__(kWave * kW32Waves, 4) void k_filter_w32(FilterArgs 
     if constexpr (kWindowed || STATS)
         if (lane < kWindowPad) L.window[lane] = L.window[kWindowWords + lane] = 0u;
     bool lds_float = false;
-    if constexpr (kStage) lds_float = stage_terms(T, terms_lds) && T.fterms != nullptr;
+    if constexpr (kStage) lds_float = (stage_terms(T, terms_lds) && T.fterms != nullptr) || kCollab;
     const bool joint = joint_texels(T, lds_float);
     auto texel = [&](int x, int y) __attribute__((always_inline)) -> float4 {
-        return texel_eval_staged<TEX>(T, terms_lds, lds_float, x, y);
+        if constexpr (kStage) return texel_eval_staged<TEX>(T, terms_lds, lds_float, x, y);
+        else return texel_eval<TEX>(T, x, y);
     };
     auto half_mask = [](uint64_t m, int hh) -> uint64_t {
         return hh ? m & 0xffffffff00000000ull : m & 0x00000000ffffffffull;
@@ -587,12 +603,21 @@ hipError_t launch_w32_m_t(const FilterArgs& a, const DevTexture& T, hipStream_t 
     constexpr bool kCollab = METHOD == CTF_LIST || METHOD == CTF_BOX || METHOD == CTF_MASK;
     // the instantiation with statistics also writes the texel lists
     const bool st = a.tile_stats != nullptr || a.lists != nullptr;
-    if (kCollab && a.fallback != CTF_FB_STF1) {
-        if (st) hipLaunchKernelGGL((k_filter_w32<METHOD, TEX, true, FILTER, kCollab>), grid, block, 0, s, a, T);
-        else hipLaunchKernelGGL((k_filter_w32<METHOD, TEX, false, FILTER, kCollab>), grid, block, 0, s, a, T);
+    auto go = [&](auto lds) {
+        constexpr bool LDS = decltype(lds)::value;
+        if (kCollab && a.fallback != CTF_FB_STF1) {
+            if (st) hipLaunchKernelGGL((k_filter_w32<METHOD, TEX, true, FILTER, kCollab, LDS>), grid, block, 0, s, a, T);
+            else hipLaunchKernelGGL((k_filter_w32<METHOD, TEX, false, FILTER, kCollab, LDS>), grid, block, 0, s, a, T);
+        } else {
+            if (st) hipLaunchKernelGGL((k_filter_w32<METHOD, TEX, true, FILTER, false, LDS>), grid, block, 0, s, a, T);
+            else hipLaunchKernelGGL((k_filter_w32<METHOD, TEX, false, FILTER, false, LDS>), grid, block, 0, s, a, T);
+        }
+    };
+    if constexpr (kCollab && TEX == CTF_TEX_SINUSOIDS) {
+        if (w32_lds_terms(T)) go(std::true_type{});
+        else go(std::false_type{});
     } else {
-        if (st) hipLaunchKernelGGL((k_filter_w32<METHOD, TEX, true, FILTER, false>), grid, block, 0, s, a, T);
-        else hipLaunchKernelGGL((k_filter_w32<METHOD, TEX, false, FILTER, false>), grid, block, 0, s, a, T);
+        go(std::false_type{});
     }
     return hipGetLastError();
 }
