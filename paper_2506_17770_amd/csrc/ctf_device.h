@@ -809,10 +809,16 @@ __device__ __forceinline__ float4 texel_eval_staged(const DevTexture& T, const i
     return texel_eval<KIND>(T, x, y);
 }
 
-// Whether sinusoid_channel_4 serves a texture (its terms staged as floats).
-__device__ __forceinline__ bool joint_texels(const DevTexture& T, bool lds_float)
+// Whether a workgroup's LDS holds a texture's terms as floats.
+__host__ __device__ __forceinline__ bool lds_terms(const DevTexture& T)
 {
-    return lds_float && T.width <= kJointWidth;
+    return T.kind == CTF_TEX_SINUSOIDS && T.fterms != nullptr && T.n_terms <= kLdsTerms;
+}
+
+// Whether sinusoid_channel_4 serves a texture.
+__host__ __device__ __forceinline__ bool joint_texels(const DevTexture& T)
+{
+    return lds_terms(T) && T.width <= kJointWidth;
 }
 
 // Texels (x, y), (x+1, y), (x, y+1), (x+1, y+1), or (ROW) (x .. x+3, y), from

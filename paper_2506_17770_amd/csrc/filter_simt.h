@@ -41,7 +41,15 @@ static_assert(kWavesPerBlock * sizeof(WaveLds<2>) + kLdsTermEntries * sizeof(int
 
 // FB: the instantiation that plans fallback C / C+ for failed waves (the
 // others fall back to one-tap STF only and carry none of that code, which
-// keeps their scalar registers for the common path).  Bilinear: five waves
+// keeps their scalar registers for the common path).  JOINT: the bilinear full
+// filter of a texture that joint_texels takes.  One kernel with the joint taps
+// and the single ones has the registers for five waves per SIMD (81); apart
+// they have eight (59) and six (79).  Joint, 32 terms: 1920x1080 140 -> 138 us,
+// 3840x2160 543 -> 533; single, 13 terms, 4096 wide: 84 -> 79 and 318 -> 306.
+// (The cubic filters choose at run time: apart, the joint form takes 107
+// registers and 2130 us at 3840x2160 in place of 95 and 2103; the 8x4 kernels
+// gain nothing.)
+// Bilinear: five waves
 // per SIMD (at most 96 vector registers; the workgroup's LDS fits five per
 // CU).  Bicubic: the LDS of the 16-tap footprints holds the occupancy lower,
 // the registers are left to the compiler.
@@ -51,7 +59,7 @@ constexpr int simt_min_waves()
     return Taps<FILTER>::F == 2 ? 5 : 1;
 }
 
-template <int METHOD, int TEX, bool STATS, int FILTER, bool FB>
+template <int METHOD, int TEX, bool STATS, int FILTER, bool FB, bool JOINT = false>
 __global__ __launch_bounds__(kWave * kWavesPerBlock, (simt_min_waves<FILTER>())) void k_filter_simt(FilterArgs a,
                                                                                                   DevTexture T)
 {
@@ -74,7 +82,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (simt_min_waves<FILTER>()))
         split_ok = kCanSplit && staged && a.split == CTF_SPLIT_AUTO;
     }
     const bool lds_float = staged && T.fterms != nullptr;
-    const bool joint = joint_texels(T, lds_float);
+    const bool joint = F == 2 ? JOINT : joint_texels(T);
     auto texel = [&](int x, int y) __attribute__((always_inline)) -> float4 {
         return texel_eval_staged<TEX>(T, terms_lds, lds_float, x, y);
     };
@@ -415,6 +423,10 @@ hipError_t launch_m_t(const FilterArgs& a, const DevTexture& T, hipStream_t s)
     if (kCollab && a.fallback != CTF_FB_STF1)
         return st ? launch_k<k_filter_simt<METHOD, TEX, true, FILTER, kCollab>>(a, T, s)
                   : launch_k<k_filter_simt<METHOD, TEX, false, FILTER, kCollab>>(a, T, s);
+    if constexpr (METHOD == CTF_BILINEAR4 && TEX == CTF_TEX_SINUSOIDS && FILTER == CTF_FILTER_BILINEAR)
+        if (joint_texels(T))
+            return st ? launch_k<k_filter_simt<METHOD, TEX, true, FILTER, false, true>>(a, T, s)
+                      : launch_k<k_filter_simt<METHOD, TEX, false, FILTER, false, true>>(a, T, s);
     return st ? launch_k<k_filter_simt<METHOD, TEX, true, FILTER, false>>(a, T, s)
               : launch_k<k_filter_simt<METHOD, TEX, false, FILTER, false>>(a, T, s);
 }

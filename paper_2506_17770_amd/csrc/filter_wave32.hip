@@ -234,22 +234,15 @@ struct HalfDecision {
     bool cap_ok, count_ok, success;
 };
 
-// Whether a collaborative launch reads its sinusoid terms from LDS.  Five
-// instructions per term need them in vector registers, from LDS by broadcast
-// (a vector instruction reads one scalar register).  Terms that are not staged
-// as floats (more than kLdsTerms, or the integer form of textures wider than
-// 4096) are scalar loads instead: as broadcast vector loads, as in the 8x8
-// kernels, which have no scalar registers left for them, Mask at 1920x1080
-// takes 258 us in place of 131 with 70 terms and 81 in place of 64 with 16
-// integer ones.
-inline bool w32_lds_terms(const DevTexture& T)
-{
-    return T.kind == CTF_TEX_SINUSOIDS && T.fterms != nullptr && T.n_terms <= kLdsTerms;
-}
-
-// LDS_TERMS (collaborative methods): w32_lds_terms; the other methods choose
-// at run time.  With the LDS slices and the staged terms four workgroups fit a
-// CU.
+// LDS_TERMS (collaborative methods): lds_terms; the other methods choose at run
+// time.  Five instructions per term need the terms in vector registers, from
+// LDS by broadcast (a vector instruction reads one scalar register).  Terms
+// that are not staged as floats (more than kLdsTerms, or the integer form of
+// textures wider than 4096) are scalar loads instead: as broadcast vector
+// loads, as in the 8x8 kernels, which have no scalar registers left for them,
+// Mask at 1920x1080 takes 258 us in place of 130 with 70 terms and 81 in place
+// of 60 with 16 integer ones.  With the LDS slices and the staged terms four
+// workgroups fit a CU.
 template <int METHOD, int TEX, bool STATS, int FILTER, bool FB, bool LDS_TERMS>
 __global__ __launch_bounds__(kWave * kW32Waves, 4) void k_filter_w32(FilterArgs a, DevTexture T)
 {
@@ -267,7 +260,7 @@ __global__ __launch_bounds__(kWave * kW32Waves, 4) void k_filter_w32(FilterArgs 
         if (lane < kWindowPad) L.window[lane] = L.window[kWindowWords + lane] = 0u;
     bool lds_float = false;
     if constexpr (kStage) lds_float = (stage_terms(T, terms_lds) && T.fterms != nullptr) || kCollab;
-    const bool joint = joint_texels(T, lds_float);
+    const bool joint = lds_float && joint_texels(T);
     auto texel = [&](int x, int y) __attribute__((always_inline)) -> float4 {
         if constexpr (kStage) return texel_eval_staged<TEX>(T, terms_lds, lds_float, x, y);
         else return texel_eval<TEX>(T, x, y);
@@ -614,7 +607,7 @@ hipError_t launch_w32_m_t(const FilterArgs& a, const DevTexture& T, hipStream_t 
         }
     };
     if constexpr (kCollab && TEX == CTF_TEX_SINUSOIDS) {
-        if (w32_lds_terms(T)) go(std::true_type{});
+        if (lds_terms(T)) go(std::true_type{});
         else go(std::false_type{});
     } else {
         go(std::false_type{});
