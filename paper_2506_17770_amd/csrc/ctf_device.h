@@ -7,6 +7,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "ctf.h"
@@ -568,17 +569,32 @@ struct FrameCounters {
         ok += okk;
         fail += fl;
     }
+    // Every lane of the wave calls this.  The eight totals of a frame are one
+    // 64-byte line, and every wave's atomics wait for it in turn: lanes 0..7 add
+    // a total each, one access per wave instead of eight.  With frame totals
+    // the List of a 1920x1080 procedural frame takes 138 us instead of 1426
+    // (B-spline 132, 1146), that of a 3840x2160 decoder frame 149 instead of 406.
     __device__ __forceinline__ void flush(ctf_frame_stats* F) const
     {
         if (!tiles) return;
-        atomicAdd((unsigned long long*)&F->evals, (unsigned long long)evals);
-        atomicAdd((unsigned long long*)&F->active, (unsigned long long)active);
-        atomicAdd((unsigned long long*)&F->stf, (unsigned long long)stf);
-        atomicAdd((unsigned long long*)&F->minify, (unsigned long long)minify);
-        atomicAdd((unsigned long long*)&F->tiles, (unsigned long long)tiles);
-        atomicAdd((unsigned long long*)&F->rows, (unsigned long long)rows);
-        atomicAdd((unsigned long long*)&F->tiles_ok, (unsigned long long)ok);
-        atomicAdd((unsigned long long*)&F->tiles_fail, (unsigned long long)fail);
+        static_assert(offsetof(ctf_frame_stats, active) == 8 && offsetof(ctf_frame_stats, stf) == 16 &&
+                          offsetof(ctf_frame_stats, minify) == 24 && offsetof(ctf_frame_stats, tiles) == 32 &&
+                          offsetof(ctf_frame_stats, tiles_ok) == 40 && offsetof(ctf_frame_stats, tiles_fail) == 48 &&
+                          offsetof(ctf_frame_stats, rows) == 56,
+                      "the order of c");
+        // (read as scalars, and the lane's index from an opaque mask: otherwise
+        // the counters are kept in vector registers for this select, and the
+        // index from the kernel's start, and the decoder kernels spill)
+        uint32_t c[8] = {evals, active, stf, minify, tiles, ok, fail, rows};
+#pragma unroll
+        for (int i = 0; i < 8; ++i) c[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)c[i]);
+        uint32_t all = ~0u;
+        asm volatile("" : "+s"(all));
+        const int lane = (int)__builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0u));
+        uint32_t v = c[0];
+#pragma unroll
+        for (int i = 1; i < 8; ++i) v = lane == i ? c[i] : v;
+        if (lane < 8) atomicAdd(reinterpret_cast<unsigned long long*>(F) + lane, (unsigned long long)v);
     }
 };
 

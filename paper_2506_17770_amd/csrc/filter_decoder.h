@@ -601,7 +601,7 @@ __global__ __launch_bounds__(64 * kDecWavesMax) void k_filter_dec(FilterArgs a, 
                                             [&](float2 uv, float4 d) {
         return footprint(uv.x, uv.y, d, tex_w, tex_w);
     });
-    if (lane == 0 && a.frame_stats) fc.flush(a.frame_stats);
+    if (a.frame_stats) fc.flush(a.frame_stats);
 }
 
 // ---------------------------------------------------------------------------
@@ -938,7 +938,7 @@ __global__ __launch_bounds__(64 * kDecWavesMax) void k_filter_dec_batch(FilterAr
     batch_walk<METHOD, P, STATS, FILTER>(a, BL, D.grid, W, Bz, TileQueue(queues, a), fc, [&](float2 uv, float4 d) {
         return wave_footprint(uv.x, uv.y, d, tex_w, tex_w);
     });
-    if (lane == 0 && a.frame_stats) fc.flush(a.frame_stats);
+    if (a.frame_stats) fc.flush(a.frame_stats);
 }
 
 // Waves of a workgroup for n units of work (tiles, or 32-texel passes): twelve
@@ -1103,7 +1103,7 @@ __global__ __launch_bounds__(64 * kDecWavesMax) void k_filter_layers(FilterArgs 
             });
         }
     }
-    if (lane == 0 && a.frame_stats) fc.flush(a.frame_stats);
+    if (a.frame_stats) fc.flush(a.frame_stats);
 }
 
 

@@ -396,7 +396,7 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (simt_min_waves<FILTER>()))
         if (act) fc.add(evals, popc64(act), nstf, popc64(act & ~A), 0, kCollab && success, kCollab && nA && !success);
         wave_lds_sync();  // the next tile reuses this wave's LDS slice
     }
-    if (lane == 0 && a.frame_stats) fc.flush(a.frame_stats);
+    if (a.frame_stats) fc.flush(a.frame_stats);
 }
 
 template <void (*K)(FilterArgs, DevTexture)>

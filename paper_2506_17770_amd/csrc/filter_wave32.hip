@@ -581,7 +581,7 @@ __global__ __launch_bounds__(kWave * kW32Waves, 4) void k_filter_w32(FilterArgs 
                        kCollab && D[hh].success, kCollab && Am[hh] && !D[hh].success);
         wave_lds_sync();  // the next pair reuses this wave's LDS slice
     }
-    if (lane == 0 && a.frame_stats) fc.flush(a.frame_stats);
+    if (a.frame_stats) fc.flush(a.frame_stats);
 }
 
 template <int METHOD, int TEX, int FILTER>

@@ -70,3 +70,21 @@ def test_8x4_terms_past_the_lds(G, frame, kind, k):
     assert past <= 1.5 * near
     for t in texs:
         t.close()
+
+
+@pytest.mark.parametrize("filt", [1, 2])
+def test_frame_totals_of_a_cubic_frame(G, frame, filt):
+    """Frame totals cost a line of atomics per wave, 8192 waves at most on this
+    kernel, which the memory serves one after the other at about 15 ns: 0.12 ms
+    on top of the frame.  One atomic per total took 1.1 ms."""
+    ctf, ctx, torch = G
+    uv, duv = frame
+    out = torch.empty((SH, SW, 4), device="cuda")
+    totals = ctf.frame_stats_buffer()
+    tex = ctx.sinusoid_texture(512, *cs.sinusoid_params(512, 32, 64, seed=1))
+    m = ctf.method(ctf.LIST, k=4, filter=filt)
+    plain, counted = times(torch, lambda: ctx.filter(uv, duv, tex, m, seed=3, out=out),
+                           lambda: ctx.filter(uv, duv, tex, m, seed=3, out=out, frame_stats=totals))
+    print(f"plain {plain:.1f} us, with totals {counted:.1f} us")
+    assert counted <= plain + 300
+    tex.close()
