@@ -40,6 +40,14 @@ constexpr int kDecWavesMax = 12, kDecWavesMin = 4;
 
 constexpr bool collaborative(int m) { return m == CTF_LIST || m == CTF_BOX || m == CTF_MASK; }
 
+// The launches whose tiles are decoded in batches: every method but the full
+// filter, without fallback C / C+ (FB).
+template <int METHOD, bool FB>
+constexpr bool batched()
+{
+    return !FB && METHOD != CTF_BILINEAR4;
+}
+
 struct DecLds {
     float4 vals[kMaxItems];     // decoded texels, by row; the List's sort before any row is decoded
     int2 rows[kMaxItems];       // texel coordinates to decode
@@ -141,6 +149,7 @@ __device__ __forceinline__ void dec_tile(const FilterArgs& a, const InferGrid& G
                                          const Biases& Bz, DecLds& L, int64_t tile, int tx, int ty,
                                          const Footprint& f, FrameCounters& fc, AfterDecode&& after_decode)
 {
+    static_assert(!batched<METHOD, FB>(), "the other calls run k_filter_dec_batch");
     constexpr int F = Taps<FILTER>::F, O = Taps<FILTER>::O;
     const int lane = lane_id();
     const int px = tx * kTile + (lane & 7), py = ty * kTile + (lane >> 3);
@@ -218,9 +227,6 @@ __device__ __forceinline__ void dec_tile(const FilterArgs& a, const InferGrid& G
     if constexpr (METHOD == CTF_BILINEAR4) {
         exact = f.active;
         draws = false;
-    } else if constexpr (METHOD == CTF_STF1) {
-        exact = false;
-        draws = f.active;
     } else {
         exact = inA && success;
         draws = f.active && !exact;
@@ -623,12 +629,6 @@ template <int F>
 constexpr int batch_slots()
 {
     return F == 2 ? 4 : 2;
-}
-
-template <int METHOD, bool FB>
-constexpr bool batched()
-{
-    return !FB && METHOD != CTF_BILINEAR4;
 }
 
 // Per wave.  vals also holds the sort of a List past 16x16: no value is live

@@ -25,7 +25,6 @@ namespace simt {
 
 constexpr int kWavesPerBlock = 4;
 
-template <int F>
 struct WaveLds {
     float4 vals[kMaxItems];         // produced texel values, by item index; the List's sort before any
     uint64_t keys[kMaxItems];       // List past 16x16: texel of each item (int2); fallback planning
@@ -36,8 +35,8 @@ struct WaveLds {
     __device__ uint8_t* byte_area() { return reinterpret_cast<uint8_t*>(window + kWindowPad); }
 };
 static_assert(sizeof(SegmentScratch<4>) <= kMaxItems * sizeof(float4), "sort in vals");
-static_assert(kWavesPerBlock * sizeof(WaveLds<2>) + kLdsTermEntries * sizeof(int4) <= 32768,
-              "a bilinear per-lane workgroup must fit five to a CU");
+static_assert(kWavesPerBlock * sizeof(WaveLds) + kLdsTermEntries * sizeof(int4) <= 32768,
+              "a per-lane workgroup must fit five to a CU");
 
 // FB: the instantiation that plans fallback C / C+ for failed waves (the
 // others fall back to one-tap STF only and carry none of that code, which
@@ -67,13 +66,13 @@ __global__ __launch_bounds__(kWave * kWavesPerBlock, (simt_min_waves<FILTER>()))
     constexpr bool kCanSplit = (METHOD == CTF_LIST || METHOD == CTF_BOX || METHOD == CTF_MASK) &&
                                TEX == CTF_TEX_SINUSOIDS;
     constexpr bool kStage = TEX == CTF_TEX_SINUSOIDS;
-    __shared__ WaveLds<F> lds_all[kWavesPerBlock];
+    __shared__ WaveLds lds_all[kWavesPerBlock];
     // the texture's terms (split rounds read them by channel; a lane's own
     // texels read them by broadcast)
     __shared__ int4 terms_lds[kStage ? kLdsTermEntries : 1];
     const int wid = wave_in_block();
     const int lane = lane_id();
-    WaveLds<F>& L = lds_all[wid];
+    WaveLds& L = lds_all[wid];
     if constexpr (METHOD == CTF_LIST || METHOD == CTF_MASK || STATS)
         if (lane < kWindowPad) L.window[lane] = 0u;
     bool staged = false, split_ok = false;
