@@ -212,7 +212,9 @@ typedef struct ctf_frame_stats {
     uint64_t tiles;       /* tiles with at least one active pixel */
     uint64_t tiles_ok;    /* tiles whose collaborative step succeeded */
     uint64_t tiles_fail;  /* tiles with a non-empty A whose step failed */
-    uint64_t rows;        /* decoder path: MLP rows issued, padding included */
+    uint64_t rows;        /* decoder path: MLP rows issued, padding included (up to 15 per
+                             decoded batch of tiles; which tiles share a batch may change
+                             from call to call, so this total may too) */
     uint64_t reserved[8];
 } ctf_frame_stats;
 

@@ -672,16 +672,15 @@ __device__ __forceinline__ float sinusoid_channel_f(TermPtr tc, int K, float xf,
     return __builtin_fmaf(0.5f, acc, 0.5f);
 }
 
-// One channel of four texels: rows y and y + dy (phase step q' dy / W), columns
-// x and x + 1, or (ROW) four columns x .. x + 3 of row y.  The phases of
-// neighbours differ by p' / W and q' / W; with W <= 2048 every sum stays below
-// 2^24 units of 1 / W even where a neighbour passes the texture's edge, so
-// each phase is exact and its fract is that of the wrapped texel: the values
-// are those of sinusoid_channel_f, in 18 (ROW: 17) instructions per term
-// instead of 20 and with one read of the term instead of four (4-tap at
-// 1920x1080, 32 terms: 154 -> 140 us, bound by the VALU: four quarter-rate
-// v_sin and 14 others per term).  Wider textures would round: they keep the
-// four evaluations.
+// One channel of four texels: columns x and x + 1 of rows y and y + 1, or (ROW)
+// columns x .. x + 3 of row y.  The phases of neighbours differ by p' / W and
+// q' / W; with W <= 2048 every sum stays below 2^24 units of 1 / W even where a
+// neighbour passes the texture's edge, so each phase is exact and its fract is
+// that of the wrapped texel: the values are those of sinusoid_channel_f, in 17
+// instructions per term instead of 20 and with one read of the term instead of
+// four (4-tap at 1920x1080, 32 terms: 154 -> 140 us, bound by the VALU: four
+// quarter-rate v_sin and 13 others per term).  Wider textures could round: they
+// keep the four evaluations.
 constexpr int kJointWidth = 2048;
 
 template <bool ROW, class TermPtr>

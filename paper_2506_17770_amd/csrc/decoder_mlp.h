@@ -295,7 +295,7 @@ struct InferGrid {
 // interpolation the two 16-texel operands of layer 1 are one exchange of
 // 16-lane rows away (infer_combine).  Together with three waves per SIMD that
 // draw their passes from a counter it took the evaluation of 2048^2 texels
-// from 129 to 58 us (the MLP's 45 GFLOP at 0.77 PFLOP/s).
+// from 129 to 59.5 us (the MLP's 45 GFLOP at 0.76 PFLOP/s).
 
 // Per-lane constants of the inference fetch (one latent level).
 template <int P>

@@ -48,10 +48,12 @@ static_assert(kWavesPerBlock * sizeof(WaveLds) + kLdsTermEntries * sizeof(int4) 
 // (The cubic filters choose at run time: apart, the joint form takes 107
 // registers and 2130 us at 3840x2160 in place of 95 and 2103; the 8x4 kernels
 // gain nothing.)
-// Bilinear: five waves
-// per SIMD (at most 96 vector registers; the workgroup's LDS fits five per
-// CU).  Bicubic: the LDS of the 16-tap footprints holds the occupancy lower,
-// the registers are left to the compiler.
+// Bilinear: five waves per SIMD (at most 96 vector registers; the workgroup's
+// LDS fits five per CU).  Bicubic: the registers are left to the compiler,
+// which takes 99 to 125 of them, four waves per SIMD.  Held to five, B-spline frames
+// of 32 terms gain at 3840x2160 (List k = 1 197 -> 191 us, k = 4 249 -> 243)
+// and lose at 640x360 (11.1 -> 11.4, with C+ 18.9 -> 19.2), and the C / C+
+// kernel spills vector registers.
 template <int FILTER>
 constexpr int simt_min_waves()
 {

@@ -13,7 +13,7 @@
 // evaluated once for the wave, whatever the halves decided: a half that
 // succeeded and one that fell back fill the lanes of the same rounds, the
 // terms come from the workgroup's LDS and the next pair's inputs are
-// requested a pair ahead (Mask with C+ at 1920x1080, 32 terms: 95 -> 73 us,
+// requested a pair ahead (Mask with C+ at 1920x1080, 32 terms: 95 -> 71 us,
 // bound by the texel evaluations and the chain of LDS steps of a tile).
 #include <type_traits>
 
